@@ -1,0 +1,419 @@
+"""Performance cases: what a user of the library has it do, through its public entry points.
+
+A dynamic graph stream is a sequence of update batches over a live edge set.  The stream
+cases keep a ring of edge sets: pass i inserts one set and deletes the oldest one, so that
+the live graph keeps its size, every update is legal (an insert of an absent edge, a delete
+of a present one), and a pass can be repeated for as long as the stream runs.  Beside the
+ring there is a fixed part of the graph that stays.  Every stream pass ends with connectivity
+queries, which complete the batch.
+
+Sizes follow the workloads of this repository's benchmark and tests: dense G(V, p) streams,
+R-MAT streams, clustered churn with bridges toggled between the clusters, streams over a
+fixed forest, query bursts between update periods, component sketches and samples of vertex
+sets, and components of the whole graph from its sketch.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_2509_14433_amd as cupk
+
+DELETE = -(1 << 63)  # bit 63 of a packed update
+U64 = (1 << 64) - 1
+
+
+def listed():
+    return [
+        # A short burst of updates between connectivity queries on a dense graph: launches
+        # and the round trip to the host count, hardly ever a structural update.
+        dict(name="burst_1k", kind="stream", edges="uniform", V=16384, live=4_000_000, churn=500),
+        # The dense ER stream in 1M-update device batches (C = 14), deletions of forest edges
+        # and their replacements among them.
+        dict(name="dense_1m", kind="stream", edges="uniform", V=16384, live=10_000_000,
+             churn=500_000),
+        # Host arrays of an R-MAT stream in 100,000-update batches: validation, packing and
+        # upload, skewed degrees, some hundred broken trees a batch.
+        dict(name="rmat_host_100k", kind="stream", edges="rmat", V=131072, live=4_000_000,
+             churn=50_000, host=True),
+        # Insertions, then deletions, over a forest that stays (V and batches odd): nearly all
+        # of the time is classification, binning and scatter at a few updates per vertex.
+        dict(name="fixed_forest_6m", kind="stream", edges="uniform", V=200_003, live=12_000_000,
+             churn=3_000_001, tree=True, phases=True),
+        # The headline churn at full size: V = 2^20, 64 clusters of 2048 vertices, an insert and
+        # a delete batch of 6.7e7 updates each, bridges between clusters toggled all along.
+        dict(name="clusters_64x2048", kind="stream", edges="clusters", V=1 << 20, clusters=64,
+             csize=2048, phases=True),
+        # A sparse graph (average degree 4): thousands of cuts a batch, so replacement rounds
+        # over thousands of pieces.
+        dict(name="sparse_cuts_20k", kind="stream", edges="uniform", V=65536, live=131_072,
+             churn=10_000),
+        # Per-update semantics: each cut undoes the speculation past it.
+        dict(name="exact_10k", kind="stream", edges="uniform", V=16384, live=1_275_000,
+             churn=5_000, mode="exact"),
+        # The multi-level hierarchy.
+        dict(name="levels_20k", kind="stream", edges="uniform", V=4096, live=400_000,
+             churn=10_000, mode="levels"),
+        # The serving loop: one request of 100,000 updates, then a burst of queries.
+        dict(name="serve_100k", kind="serve", edges="uniform", V=65536, live=8_000_000,
+             churn=50_000, queries=64),
+        # Aggregate sketches of 200 vertex sets of very different sizes into device memory.
+        dict(name="aggregate_60k", kind="aggregate", V=131072, live=2_000_000, sets=200,
+             members=60_000),
+        # One small set's cut sketch and a sample of its cut, as a user looks for an edge.
+        dict(name="cut_query_37", kind="query", V=16384, live=1_000_000, sets=1, members=37),
+        # Components of the whole graph from the vertex sketches alone.
+        dict(name="static_65536", kind="static", V=65536, live=1_000_000),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case of the same ranges."""
+    kind = rng.choice(["stream", "stream", "stream", "clusters", "mode", "serve", "aggregate",
+                       "query", "static"])
+    if kind == "clusters":
+        n = rng.randrange(2, 33)
+        return dict(kind="stream", edges="clusters", V=n * rng.randrange(9000, 16385), clusters=n,
+                    csize=2048, phases=True)
+    if kind == "mode":
+        mode = rng.choice(["exact", "levels", "graph"])
+        V = _log(rng, 1024, 8192)
+        churn = _log(rng, 300, 5000)
+        return dict(kind="stream", edges="uniform", V=V, live=rng.randrange(40, 60) * V,
+                    churn=churn, mode=mode)
+    V = _log(rng, 2048, 150_000)
+    if kind == "stream":
+        churn = _log(rng, 150, 3_000_000)
+        churn = min(churn, V * (V - 1) // 16)
+        edges = rng.choice(["uniform", "uniform", "rmat"])
+        if edges == "rmat":  # V a power of two; skewed pairs repeat, so fewer of them
+            V = 1 << max(13, V.bit_length() - 1)
+            churn = min(churn, 6 * V)
+        tree = churn > 500_000 or rng.random() < 0.4
+        live = churn * rng.randrange(2, 5) if tree else max(20 * churn, 4 * V)
+        live = min(live, 12_000_000, V * (V - 1) // (16 if edges == "rmat" else 4))
+        return dict(kind="stream", edges=edges, V=V, live=max(live, 2 * churn), churn=churn,
+                    tree=tree, phases=rng.random() < 0.3, host=churn < 200_000 and
+                    rng.random() < 0.4)
+    live = min(rng.randrange(4, 16) * V, 2_000_000)
+    if kind == "serve":
+        return dict(kind="serve", edges="uniform", V=V, live=max(live, 4 * V),
+                    churn=min(_log(rng, 300, 100_000), live // 8), queries=rng.randrange(1, 200))
+    if kind == "aggregate":
+        return dict(kind="aggregate", V=V, live=live, sets=_log(rng, 1, 1000),
+                    members=_log(rng, 100, V))
+    if kind == "query":
+        return dict(kind="query", V=V, live=live, sets=_log(rng, 1, 64), members=_log(rng, 1, 2000))
+    V = _log(rng, 1024, 65536)
+    return dict(kind="static", V=V, live=rng.randrange(4, 16) * V)
+
+
+# ---- edges -----------------------------------------------------------------
+
+
+def _gen(seed):
+    return torch.Generator(device="cuda").manual_seed(seed)
+
+
+def _keys(case, need, g, avoid=None):
+    """`need` distinct edges {u, v} as u * V + v, u < v, in random order."""
+    V, have = case["V"], torch.empty(0, dtype=torch.int64, device="cuda")
+    while have.numel() < need:
+        m = int((need - have.numel()) * 1.25) + 64
+        if case.get("edges") == "rmat":
+            u = torch.zeros(m, dtype=torch.int64, device="cuda")
+            v = torch.zeros(m, dtype=torch.int64, device="cuda")
+            for _ in range(V.bit_length() - 1):  # quadrants (0.57, 0.19, 0.19, 0.05)
+                r = torch.rand(m, generator=g, device="cuda")
+                u = 2 * u + (r >= 0.76).long()
+                v = 2 * v + (((r >= 0.57) & (r < 0.76)) | (r >= 0.95)).long()
+        else:
+            u = torch.randint(V, (m,), generator=g, device="cuda")
+            v = torch.randint(V, (m,), generator=g, device="cuda")
+        k = torch.minimum(u, v) * V + torch.maximum(u, v)
+        k = k[u != v]
+        if avoid is not None:
+            k = k[~torch.isin(k, avoid)]
+        have = torch.unique(torch.cat([have, k]))
+    return have[torch.randperm(have.numel(), generator=g, device="cuda")[:need]]
+
+
+def _tree(n, g):
+    """A random recursive tree over vertices 0..n-1: its n - 1 edges as (parent, child)."""
+    c = torch.arange(1, n, device="cuda")
+    p = (torch.rand(n - 1, generator=g, device="cuda", dtype=torch.float64) * c).long()
+    return torch.minimum(p, c - 1), c
+
+
+def _ring(case, seed):
+    """(edges that stay, ring of edge sets [K, churn]) as keys; all but the last set of the ring
+    are live before the first pass."""
+    g = _gen(seed)
+    V, churn, live = case["V"], case["churn"], case["live"]
+    k = max(2, min(256, live // churn + 1))
+    tree = None
+    if case.get("tree"):
+        p, c = _tree(V, g)
+        tree = p * V + c
+    keys = _keys(case, live + churn, g, tree)
+    ring = keys[: k * churn].view(k, churn)
+    stay = keys[k * churn:]
+    return (stay if tree is None else torch.cat([tree, stay])), ring, g
+
+
+def _packed(keys, V):
+    u = keys // V
+    return u | (keys - u * V) << 32
+
+
+def _shuffled(x, g):
+    return x[torch.randperm(x.numel(), generator=g, device="cuda")]
+
+
+def _stream_calls(case, ring, g):
+    """The calls of pass i, for each i of the ring: pass i inserts set i - 1 and deletes set i."""
+    V, k = case["V"], ring.shape[0]
+    passes = []
+    for i in range(k):
+        ins, dele = _packed(ring[i - 1], V), _packed(ring[i], V) | DELETE
+        if case.get("phases"):
+            passes.append([_shuffled(ins, g), _shuffled(dele, g)])
+        else:
+            passes.append([_shuffled(torch.cat([ins, dele]), g)])
+    return passes
+
+
+def _cluster_stream(case, seed):
+    """(setup batch, passes): a sparse G(n, 2n) beside the clusters, a random tree in each
+    cluster, bridges between clusters; pass i inserts half i - 1 of the other cluster pairs and
+    deletes half i, with 100 random bridges toggled every 100,000 updates."""
+    g = _gen(seed)
+    V, nc, s = case["V"], case["clusters"], case["csize"]
+    n0 = nc * s  # vertices in clusters: 0 .. n0 - 1
+    sparse = _keys(dict(V=V - n0), 2 * (V - n0), g)
+    su = sparse // (V - n0)
+    sparse = (su + n0) | (sparse - su * (V - n0) + n0) << 32
+    p, c = _tree(s, g)
+    base = (torch.arange(nc, device="cuda") * s)[:, None]
+    forest = ((p + base) | (c + base) << 32).reshape(-1)
+    # bridges: a random tree over the clusters and as many more between random ones, each at
+    # vertices of its own; a random half of them is live at first
+    a, b = _tree(nc, g)
+    more = torch.randint(nc, (nc + 1,), generator=g, device="cuda")
+    step = torch.randint(nc - 1, (nc + 1,), generator=g, device="cuda") + 1
+    a, b = torch.cat([a, more]), torch.cat([b, (more + step) % nc])
+    nb = a.numel()
+    at = torch.randperm(s, generator=g, device="cuda")[:nb]
+    bridges = (a * s + at) | (b * s + at) << 32
+    live = torch.rand(nb, generator=g, device="cuda") < 0.5
+    setup = torch.cat([_shuffled(sparse, g), forest, bridges[live]])
+    # every other pair of a cluster, split into two halves
+    mask = torch.ones(s, s, dtype=torch.bool, device="cuda").triu_(1)
+    mask[p, c] = False
+    u, v = mask.nonzero(as_tuple=True)
+    pairs = ((u | v << 32)[None, :] + (base | base << 32)).reshape(-1)
+    pairs = _shuffled(pairs, g)
+    half = pairs.numel() // 2
+    sets = [pairs[:half], pairs[half: 2 * half]]
+    del pairs, mask, u, v
+
+    # the toggles of pass 0; pass 1 takes them back in reverse order
+    every, per = 100_000, 100
+    seg = half // every
+    t = torch.randint(nb, (2 * seg * per,), generator=g, device="cuda")
+    hit = torch.nn.functional.one_hot(t, nb).to(torch.int32)
+    before = (hit.cumsum(0) - hit)[torch.arange(t.numel(), device="cuda"), t] + live[t].int()
+    toggle = bridges[t] | torch.where(before % 2 == 1, DELETE, 0)
+    passes = []
+    for i, tog in enumerate((toggle, (toggle ^ DELETE).flip(0))):
+        calls = []
+        for keys, tg in ((sets[i - 1], tog[: seg * per]), (sets[i] | DELETE, tog[seg * per:])):
+            keys = _shuffled(keys, g)
+            head = torch.cat([keys[: seg * every].view(seg, every), tg.view(seg, per)], 1)
+            calls.append(torch.cat([head.reshape(-1), keys[seg * every:]]))
+        passes.append(calls)
+    # the last set of the ring of two is the one pass 0 inserts
+    return [setup, _shuffled(sets[0], g)], passes
+
+
+def _host(packed):
+    w = packed.cpu().numpy().view(np.uint64)
+    return ((w & np.uint64(0xFFFFFFFF)).astype(np.uint32),
+            ((w >> np.uint64(32)) & np.uint64(0x7FFFFFFF)).astype(np.uint32),
+            (w >> np.uint64(63)).astype(np.uint8))
+
+
+def _context(case, seed, batch):
+    mode = case.get("mode")
+    return cupk.Context(case["V"], seed=seed, max_batch=batch, exact=mode == "exact",
+                        levels=mode == "levels", use_graph=mode == "graph")
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    g = _gen(seed + 7)
+    V = case["V"]
+    if kind in ("stream", "serve"):
+        if case["edges"] == "clusters":
+            setup, passes = _cluster_stream(case, seed)
+        else:
+            stay, ring, rg = _ring(case, seed)
+            first = torch.cat([stay, ring[:-1].reshape(-1)])
+            # the forest is of the edges that come first: those that stay where they are most
+            if not case.get("tree") and ring.numel() > stay.numel():
+                first = _shuffled(first, rg)
+            setup = [_packed(first, V)]
+            passes = _stream_calls(case, ring, rg)
+        batch = max(c.numel() for c in passes[0])
+        ctx = _context(case, seed, batch)
+        if case.get("mode") == "exact":  # the same graph, inserted only: no cut on the way
+            batch = 1 << 20
+        for part in setup:
+            for o in range(0, part.numel(), max(batch, 1 << 20)):
+                ctx.apply_updates_device(part[o: o + max(batch, 1 << 20)].contiguous())
+        ctx.sync()
+        if case.get("host") or kind == "serve":
+            passes = [[_host(c) for c in calls] for calls in passes]
+        q = torch.randint(V, (2, case.get("queries", 8)), generator=g, device="cuda").cpu()
+        state = dict(kind=kind, ctx=ctx, passes=passes, step=0, host=bool(case.get("host")),
+                     qu=q[0].tolist(), qv=q[1].tolist())
+        if kind == "serve":
+            state["qu"], state["qv"] = q.numpy().astype(np.uint32)
+            ctx.serve_start()
+        return state
+    keys = _keys(dict(V=V), case["live"], _gen(seed))
+    ctx = _context(case, seed, case["live"])
+    ctx.apply_updates_device(_packed(keys, V))
+    ctx.sync()
+    state = dict(kind=kind, ctx=ctx)
+    if kind != "static":
+        rng = np.random.default_rng(seed)
+        # sets of very different sizes: exponential shares of the members
+        share = rng.exponential(size=case["sets"]) ** 2
+        size = np.maximum(1, share / share.sum() * case["members"]).astype(np.int64)
+        state["sets"] = [rng.choice(V, min(int(n), V), replace=False).astype(np.uint32)
+                         for n in size]
+    if kind == "aggregate":
+        state["out"] = torch.empty(case["sets"] * ctx.C * ctx.D * 2, dtype=torch.int64,
+                                   device="cuda")
+    return state
+
+
+def run(state):
+    ctx, kind = state["ctx"], state["kind"]
+    if kind == "stream":
+        calls = state["passes"][state["step"] % len(state["passes"])]
+        state["step"] += 1
+        for c in calls:
+            if state["host"]:
+                ctx.apply_updates(*c)
+            else:
+                ctx.apply_updates_device(c)
+        answers = [ctx.connected(a, b) for a, b in zip(state["qu"], state["qv"])]
+        return {"sketch": ctx.sketch_tensor, "connected": answers,
+                "components": ctx.num_components()}
+    if kind == "serve":
+        calls = state["passes"][state["step"] % len(state["passes"])]
+        state["step"] += 1
+        tickets = [ctx.submit_updates(*c) for c in calls]
+        t, answers = ctx.submit_queries(state["qu"], state["qv"])
+        done = [ctx.wait(x) for x in tickets] + [ctx.wait(t)]
+        return {"sketch": ctx.sketch_tensor, "connected": answers, "status": done}
+    if kind == "aggregate":
+        return ctx.component_sketch_batch(state["sets"], out=state["out"])
+    if kind == "query":
+        alpha, gamma = ctx.component_sketch_batch(state["sets"])
+        status, u, v = ctx.sample_cut_edge_batch(alpha, gamma)
+        return {"alpha": alpha.view(np.int64), "gamma": gamma.view(np.int64), "status": status,
+                "u": u, "v": v}
+    labels, edges, info = ctx.static_components()
+    return {"labels": labels, "edges": np.array(edges, np.int64).reshape(-1, 2),
+            "rounds": info["rounds"], "components": info["n_components"]}
+
+
+def _columns(V):
+    L = max(1, (V - 1).bit_length())
+    return L, 2 * L
+
+
+def _changed_buckets(V, C, D, records):
+    """Buckets that `records` endpoint records spread over V vertices change, about."""
+    r = records / V
+    per = sum(1 - (1 - 2.0 ** -(d + 1)) ** r for d in range(D))
+    return V * C * per
+
+
+def work(case):
+    """Bytes: updates and members read, changed buckets read and written, aggregates written.
+    flops: the integer operations of one hash of each edge and column (19 a hash)."""
+    V, kind = case["V"], case["kind"]
+    C, D = _columns(V)
+    slab = C * D * 16
+    if kind in ("stream", "serve"):
+        if case["edges"] == "clusters":
+            n0 = case["clusters"] * case["csize"]
+            n = n0 * (case["csize"] - 1) // 2  # two halves of the pairs
+            changed = 2 * _changed_buckets(n0, C, D, n)
+        else:
+            n = 2 * case["churn"]
+            calls = 2 if case.get("phases") else 1
+            changed = calls * _changed_buckets(V, C, D, 2 * n / calls)
+        return {"bytes": 8 * n + 32 * changed, "flops": 19 * C * n}
+    if kind == "static":
+        return {"bytes": V * slab + 4 * V, "flops": 19 * C * D * V}
+    return {"bytes": (case["members"] + case["sets"]) * slab, "flops": 0}
+
+
+# ---- the same results from the definition ------------------------------------
+
+
+def _mix(z):
+    m = np.uint64
+    z = (z ^ (z >> m(30))) * m(0xBF58476D1CE4E5B9)
+    z = (z ^ (z >> m(27))) * m(0x94D049BB133111EB)
+    return z ^ (z >> m(31))
+
+
+def _sketch(keys, V, seed):
+    """The sketch of the graph with these edges, from its definition, [vertex][depth][column]
+    of (index, checksum)."""
+    C, D = _columns(V)
+    x = keys.cpu().numpy().astype(np.uint64)
+    ends = [(x // np.uint64(V)).astype(np.int64), (x % np.uint64(V)).astype(np.int64)]
+    out = np.zeros((V * D * C, 2), np.uint64)
+    state = seed & U64
+    for c in range(C):
+        state = (state + 0x9E3779B97F4A7C15) & U64
+        h = _mix(x ^ _mix(np.array([state], np.uint64)))
+        low = h & (~h + np.uint64(1))
+        d = np.where(h == 0, D - 1, np.minimum(np.log2(np.maximum(low, 1).astype(np.float64)),
+                                               D - 1)).astype(np.int64)
+        for w in ends:
+            at = (w * D + d) * C + c
+            order = np.argsort(at)
+            first = np.flatnonzero(np.r_[True, np.diff(at[order]) != 0])
+            for j, words in enumerate((x, h)):
+                out[at[order][first], j] ^= np.bitwise_xor.reduceat(words[order], first)
+    return out.reshape(-1).view(np.int64)
+
+
+def exact(case, seed):
+    if case["kind"] not in ("stream", "serve") or case["edges"] == "clusters":
+        return None
+    V = case["V"]
+    C, _ = _columns(V)
+    if (case["live"] + (V if case.get("tree") else 0)) * C > 8_000_000:
+        return None
+    stay, ring, _ = _ring(case, seed)
+    live = torch.cat([stay, ring[1:].reshape(-1)])
+    none = [None] * case.get("queries", 8)
+    got = {"sketch": _sketch(live, V, seed), "connected": none}
+    if case["kind"] == "stream":
+        return got | {"components": None}
+    return got | {"connected": None, "status": [None, None]}
