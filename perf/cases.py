@@ -333,8 +333,8 @@ def run(state):
         return {"alpha": alpha.view(np.int64), "gamma": gamma.view(np.int64), "status": status,
                 "u": u, "v": v}
     labels, edges, info = ctx.static_components()
-    return {"labels": labels, "edges": np.array(edges, np.int64).reshape(-1, 2),
-            "rounds": info["rounds"], "components": info["n_components"]}
+    return {"labels": labels, "edges": len(edges), "rounds": info["rounds"],
+            "components": info["n_components"]}
 
 
 def _columns(V):
