@@ -69,8 +69,9 @@ extern "C" {
 #define CUPK_SCATTER_STAGED 1 /* vertex-binned, LDS-staged kernel              */
 
 /* ---- staged-scatter lane layouts --------------------------------------- */
-#define CUPK_LAYOUT_RECORD 1  /* one lane per record, its C columns in turn    */
-#define CUPK_LAYOUT_PAIR 2    /* one lane per (record, column) pair            */
+#define CUPK_LAYOUT_RECORD 1  /* one lane per record: up to 24 columns both    */
+#define CUPK_LAYOUT_PAIR 2    /* run that kernel, beyond both the one with one
+                                 lane per (record, column) pair                */
 
 typedef struct cupk_ctx cupk_ctx;
 
@@ -107,8 +108,9 @@ typedef struct {
      * vertices per LDS tile and depth rows kept in LDS. */
     uint32_t tile_vertices;
     uint32_t lds_rows;
-    /* Records per work item of the staged kernel (0 = default 4096) and
-     * blocks of its persistent grid (0 = default 2048). */
+    /* Records per work item of the staged kernel (0 = default: 4096, more
+     * for batches above 2M updates) and blocks of its persistent grid (0 =
+     * default: as many as fit, more for dense batches). */
     uint32_t chunk_records;
     uint32_t tile_grid;
     /* Nonzero: replay each batch's device work (classification with its
@@ -165,13 +167,10 @@ typedef struct {
      * fill reserves), so that the fill reserves nothing.  Same bins up to
      * the order of records inside a tile, same sketch. */
     uint32_t fill_reserve;
-    /* Lane layout of the staged scatter: CUPK_LAYOUT_RECORD (each lane
-     * hashes one record's C columns as independent chains; LDS address
-     * conflicts grow with the records per vertex and batch) or
-     * CUPK_LAYOUT_PAIR (each lane one (record, column) pair, records decoded
-     * once into LDS; conflict-free, for large batches).  0 = default: PAIR
-     * when max_batch is at least 4M updates, else RECORD.  The autotuner
-     * tries both. */
+    /* Lane layout of the staged scatter: CUPK_LAYOUT_RECORD, CUPK_LAYOUT_PAIR
+     * or 0.  The kernel follows from the number of columns (see the
+     * constants), so this only decides which tile geometries are accepted:
+     * RECORD admits a delta of 64 KiB, PAIR one of 52 KiB. */
     uint32_t tile_layout;
     /* Nonzero: finish each batch's replacement rounds before the next batch
      * is classified.  Default: when a device batch follows one whose host

@@ -895,6 +895,19 @@ void drop_graphs(cupk_ctx *ctx)
     ctx->graph_cap = 0;
 }
 
+// Records per work item of a batch of n updates: the chosen number, or by
+// default as many as leave 1,024 items (a tile is then folded once, by one
+// block, without atomics, unless it holds more than its share), at least
+// 4,096.  3.4e7 records on 32,768 vertices in 16-vertex tiles: 0.44 ms with
+// 32,768 records per item (one item per tile), 0.49 with 8,192 (two).
+static uint32_t batch_chunk(const cupk_ctx *ctx, uint32_t n)
+{
+    uint32_t c = ctx->chunk;
+    if (ctx->chunk_auto)
+        while (c < (1u << 30) && (uint64_t)c * 1024 < 2 * (uint64_t)n) c *= 2;
+    return c;
+}
+
 StagedParams staged_params(cupk_ctx *ctx, uint32_t grid_n)
 {
     StagedParams p;
@@ -902,9 +915,10 @@ StagedParams staged_params(cupk_ctx *ctx, uint32_t grid_n)
     p.rows = ctx->rows;
     p.layout = ctx->layout == CUPK_LAYOUT_PAIR ? kLayoutPair : kLayoutRecord;
     p.ntiles = ctx->ntiles;
-    p.chunk = ctx->chunk;
-    p.items_cap = (uint32_t)(2 * (size_t)grid_n / ctx->chunk + ctx->ntiles + 1);
+    p.chunk = batch_chunk(ctx, grid_n);
+    p.items_cap = (uint32_t)(2 * (size_t)grid_n / p.chunk + ctx->ntiles + 1);
     p.grid = ctx->tile_grid;
+    p.records = 2 * (uint64_t)grid_n;
     return p;
 }
 
@@ -939,8 +953,9 @@ int enqueue_classify(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n, bool tiles_o
         sa.cur = ctx->d_tcur.p;
         sa.items = ctx->d_items.p;
         sa.nitems = ctx->d_nitems;
-        sa.chunk = ctx->chunk;
-        sa.items_cap = staged_params(ctx, grid_n).items_cap;
+        const StagedParams p = staged_params(ctx, grid_n);
+        sa.chunk = p.chunk;
+        sa.items_cap = p.items_cap;
         sa.groups = 1;
         if (ctx->ntiles > kScanOneBlockTiles) sa.sums = ctx->d_tsum.p;
     }
@@ -995,7 +1010,7 @@ int enqueue_bin(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n)
     sa.cur = ctx->d_tcur.p;
     sa.items = ctx->d_items.p;
     sa.nitems = ctx->d_nitems;
-    sa.chunk = ctx->chunk;
+    sa.chunk = p.chunk;
     sa.items_cap = p.items_cap;
     sa.groups = 1;
     sa.sums = ctx->d_tsum.p;
@@ -1678,6 +1693,7 @@ int set_geometry(cupk_ctx *ctx, uint32_t tv, uint32_t rows, uint32_t chunk, uint
         return ctx->invalid("staged tile does not fit 64 KiB of LDS (with the record stage of "
                             "the pair layout)");
     if (chunk < 64) return ctx->invalid("chunk_records must be >= 64");
+    ctx->chunk_auto = false;
     ctx->tile_shift = sh;
     ctx->rows = rows;
     ctx->chunk = chunk;
@@ -1826,15 +1842,27 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     }
     ctx->forest_dev_stale = true;
 
-    // staged scatter geometry: LDS delta of `rows` depth rows x C columns x
-    // 2 words per vertex, at most 64 KiB per block
+    // Staged scatter geometry: LDS delta of `rows` depth rows x C columns x
+    // 2 words per vertex.  By default 16 vertices per tile, fewer where that
+    // would leave less than 768 tiles (three blocks per CU), and as many rows
+    // up to 12 as let three blocks share a CU's LDS (every row halves the
+    // pairs that go to HBM one by one): 2.0e6 records on 16,384 vertices,
+    // C = 14, take 0.033 ms in 16-vertex tiles with 11 rows, 0.035 in
+    // 8-vertex tiles, 0.034 with 8 rows.
     uint32_t rows = ctx->opts.lds_rows ? ctx->opts.lds_rows : 8;
     rows = std::min(rows, D);
     uint32_t tv = ctx->opts.tile_vertices;
-    if (tv == 0) {
-        // measured best on the V=16384, C=14 workload: 16 vertices per tile
-        // (about 28 KiB of LDS, several blocks per CU); smaller when C*rows
-        // does not fit
+    if (tv == 0 && C <= kStagMaxC) {
+        tv = V >= 16 * 768 ? 16 : V >= 8 * 768 ? 8 : 4;
+        auto fits = [&](uint32_t r, uint32_t t) {
+            return tile_geometry_fits(r, C, t, kLayoutPair) &&
+                   ((size_t)(r + 1) * t + 1) * C * 16 <= 163840 / 3;
+        };
+        while (tv > 1 && !fits(rows, tv)) tv /= 2;
+        if (ctx->opts.lds_rows == 0)
+            while (rows < std::min(12u, D) && fits(rows + 1, tv)) rows++;
+    } else if (tv == 0) {
+        // pair kernel: about 28 KiB of LDS, several blocks per CU
         tv = 1;
         while ((size_t)2 * rows * C * (tv * 2) * 8 <= 32768 && tv < 16) tv *= 2;
     }
@@ -1845,6 +1873,7 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     int rc0 = set_geometry(ctx, tv, rows, ctx->opts.chunk_records ? ctx->opts.chunk_records : 4096,
                            layout, ctx->opts.coarse_tiles);
     if (rc0 != CUPK_OK) return rc0;
+    ctx->chunk_auto = ctx->opts.chunk_records == 0;
     const size_t mb = ctx->opts.max_batch ? ctx->opts.max_batch : (1u << 20);
     int rc = ensure_batch_buffers(ctx, mb);
     if (rc != CUPK_OK) return rc;
@@ -2432,52 +2461,50 @@ int cupk_autotune(cupk_ctx *ctx, const uint64_t *d_sample, size_t n, cupk_tune_r
         HIPCHK(hipEventCreate(&e1));
         const uint32_t tv0 = 1u << ctx->tile_shift, rows0 = ctx->rows, chunk0 = ctx->chunk;
         const uint32_t lay0 = ctx->layout;
+        const bool auto0 = ctx->chunk_auto;
         const uint32_t co0 = ctx->fshift ? 1u << ctx->fshift : 0u;
         const uint32_t m = (uint32_t)n;
         double before = 0;
         rc = time_scatter(ctx, d_sample, m, 1, e0, e1, &before);  // also warms up
         if (rc == CUPK_OK) rc = time_scatter(ctx, d_sample, m, 2, e0, e1, &before);
         double best = before;
-        uint32_t btv = tv0, brows = rows0, bchunk = chunk0, blay = lay0, tried = 1;
+        const uint32_t chunk1 = batch_chunk(ctx, m);  // records per item just timed
+        uint32_t btv = tv0, brows = rows0, bchunk = chunk1, blay = lay0, tried = 1;
         struct Cand {
             double ms;
             uint32_t tv, rows, chunk, lay;
         };
         std::vector<Cand> cands;
-        cands.push_back({before, tv0, rows0, chunk0, lay0});
-        const uint32_t lays[] = {CUPK_LAYOUT_RECORD, CUPK_LAYOUT_PAIR};
+        cands.push_back({before, tv0, rows0, chunk1, lay0});
         const uint32_t tvs[] = {4, 8, 16, 32, 64};
         const uint32_t rowss[] = {6, 8, 10, 12};
-        const uint32_t chunks[] = {2048, 4096, 8192};
-        for (uint32_t lay : lays)
-            for (uint32_t tv : tvs)
-                for (uint32_t rows : rowss)
-                    for (uint32_t ch : chunks) {
-                        if (rc != CUPK_OK) break;
-                        if (rows > ctx->D || !tile_geometry_fits(rows, ctx->C, tv,
-                                                                 lay == CUPK_LAYOUT_PAIR
-                                                                     ? kLayoutPair
-                                                                     : kLayoutRecord))
-                            continue;
-                        if (tv == tv0 && rows == rows0 && ch == chunk0 && lay == lay0 && !co0)
-                            continue;
-                        rc = set_geometry(ctx, tv, rows, ch, lay, 0);
-                        if (rc != CUPK_OK) break;
-                        double ms = 0;
-                        rc = time_scatter(ctx, d_sample, m, 2, e0, e1, &ms);
-                        tried++;
-                        if (ctx->trace)
-                            fprintf(stderr, "cupk tune layout=%u tv=%u rows=%u chunk=%u %.4f ms\n",
-                                    lay, tv, rows, ch, ms);
-                        if (rc == CUPK_OK) cands.push_back({ms, tv, rows, ch, lay});
-                        if (rc == CUPK_OK && ms < best) {
-                            best = ms;
-                            btv = tv;
-                            brows = rows;
-                            bchunk = ch;
-                            blay = lay;
-                        }
+        const uint32_t chunks[] = {4096, 16384, 65536};
+        // (both layouts run the same kernel: one of them is enough)
+        const uint32_t lay = CUPK_LAYOUT_RECORD;
+        for (uint32_t tv : tvs)
+            for (uint32_t rows : rowss)
+                for (uint32_t ch : chunks) {
+                    if (rc != CUPK_OK) break;
+                    if (rows > ctx->D || !tile_geometry_fits(rows, ctx->C, tv, kLayoutRecord))
+                        continue;
+                    if (tv == tv0 && rows == rows0 && ch == chunk1 && !co0) continue;
+                    rc = set_geometry(ctx, tv, rows, ch, lay, 0);
+                    if (rc != CUPK_OK) break;
+                    double ms = 0;
+                    rc = time_scatter(ctx, d_sample, m, 2, e0, e1, &ms);
+                    tried++;
+                    if (ctx->trace)
+                        fprintf(stderr, "cupk tune layout=%u tv=%u rows=%u chunk=%u %.4f ms\n",
+                                lay, tv, rows, ch, ms);
+                    if (rc == CUPK_OK) cands.push_back({ms, tv, rows, ch, lay});
+                    if (rc == CUPK_OK && ms < best) {
+                        best = ms;
+                        btv = tv;
+                        brows = rows;
+                        bchunk = ch;
+                        blay = lay;
                     }
+                }
         // The best few again, in two alternating passes of twice the
         // repetitions: settings within a few percent of each other are
         // within the noise of one short timing, and a wrong pick among them
@@ -2576,6 +2603,7 @@ int cupk_autotune(cupk_ctx *ctx, const uint64_t *d_sample, size_t n, cupk_tune_r
         (void)hipEventDestroy(e1);
         if (rc != CUPK_OK) {
             (void)set_geometry(ctx, tv0, rows0, chunk0, lay0, co0);
+            ctx->chunk_auto = auto0;
             return rc;
         }
         out->tile_layout = blay;

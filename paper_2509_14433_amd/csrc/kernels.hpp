@@ -80,10 +80,14 @@ struct ScanArgs {
 };
 uint32_t tile_scan_chunks(uint32_t ntiles);
 
-// Staged-scatter lane layouts: one lane per record (its C columns in turn)
-// or one lane per (record, column) pair.
+// Staged-scatter lane layouts a caller may name.  Up to kStagMaxC columns
+// both run k_tile_scatter_stag (one lane per record, staggered columns),
+// which is the faster one at every size measured; beyond, k_tile_scatter
+// (one lane per (record, column) pair, any number of columns).  They only
+// differ in the geometry they admit (tile_geometry_fits).
 constexpr uint32_t kLayoutRecord = 1;
 constexpr uint32_t kLayoutPair = 2;
+constexpr uint32_t kStagMaxC = 24;
 
 struct StagedParams {
     uint32_t tile_shift;   // vertices per tile = 1 << tile_shift
@@ -93,6 +97,7 @@ struct StagedParams {
     uint32_t chunk;        // max records per work item
     uint32_t items_cap;    // capacity of the work-item array
     uint32_t grid;         // blocks of the persistent tile kernel (0 = default)
+    uint64_t records;      // endpoint records of the batch (two per update), at most
 };
 
 // Per-batch: validation, structural classification and compaction of the
