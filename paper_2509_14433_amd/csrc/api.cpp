@@ -924,8 +924,8 @@ StagedParams staged_params(cupk_ctx *ctx, uint32_t grid_n)
 
 // Device work of one batch, in three parts.  Grids are sized for grid_n;
 // the kernels read the batch from ctx->cur_desc (by value) or, while graphs
-// are captured, from ctx->d_desc.  The header is left zeroed by the previous
-// batch's scatter (and at init).
+// are captured, from ctx->d_desc.  The header's error word is left zeroed by
+// the scan after the previous batch's classification (and at init).
 static const BatchDesc *desc_ptr(cupk_ctx *ctx) { return ctx->capturing ? ctx->d_desc : nullptr; }
 
 // Where the scan after classification finds the flag regions (and puts a
@@ -1856,7 +1856,7 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
         tv = V >= 16 * 768 ? 16 : V >= 8 * 768 ? 8 : 4;
         auto fits = [&](uint32_t r, uint32_t t) {
             return tile_geometry_fits(r, C, t, kLayoutPair) &&
-                   ((size_t)(r + 1) * t + 1) * C * 16 <= 163840 / 3;
+                   ((size_t)(r + 1) * t + 1) * C * 16 <= 53248;
         };
         while (tv > 1 && !fits(rows, tv)) tv /= 2;
         if (ctx->opts.lds_rows == 0)

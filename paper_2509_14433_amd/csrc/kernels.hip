@@ -149,7 +149,14 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(uint32_t *__restrict
     __shared__ uint32_t sh[160];
     __shared__ uint32_t boff[kInlineMaxBlocks];
     static_assert(kInlineFlags < 65536 && kClsPerBlock < 65536, "packed region words");
-    const bool err = hdr[HDR_ERR] != 0;
+    // the batch's verdict moves to HDR_REJ, which every later kernel of the
+    // pass reads, and ERR is cleared for the next classification
+    const bool err = hdr[fi.checked ? HDR_REJ : HDR_ERR] != 0;
+    __syncthreads();
+    if (threadIdx.x == 0 && !fi.checked) {
+        hdr[HDR_REJ] = err ? 1u : 0u;
+        hdr[HDR_ERR] = 0;
+    }
     if (!fi.tiles_only) {
         // the batch's flag counts: sums of the classify blocks' counts
         uint32_t nflag, nflag_del;
@@ -196,9 +203,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(uint32_t *__restrict
         // the header goes straight to host memory (no copy, no event): words
         // first, then the sequence number with release semantics
         if (threadIdx.x == 0) {
-            hout[HDR_ERR] = hdr[HDR_ERR];
-            hdr[HDR_NFLAG] = nflag;
-            hdr[HDR_NFLAG_DEL] = nflag_del;
+            hout[HDR_ERR] = err ? 1u : 0u;
             hout[HDR_NFLAG] = nflag;
             hout[HDR_NFLAG_DEL] = nflag_del;
             hout[HDR_INLINE] = inl ? 1u : 0u;
@@ -304,7 +309,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_offsets(uint32_t *__restr
                                                                const uint32_t *__restrict__ hdr)
 {
     __shared__ uint32_t sh[160];
-    const bool err = hdr[HDR_ERR] != 0;
+    const bool err = hdr[HDR_REJ] != 0;
     const uint32_t b = blockIdx.x;
     // totals of the chunks before this one
     uint32_t pc = 0, pk = 0;
@@ -607,12 +612,8 @@ hipError_t launch_classify(hipStream_t s, const BatchDesc *desc, BatchDesc dv, u
         tile_rel);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // (nothing to do for the one-block scan when it only scans tiles and
-    // the multi-block kernels do that, or there are no tile counts)
-    if (!fi.tiles_only || (tile_cnt && sa.off && !sa.sums)) {
-        k_tile_scan<<<1, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa, hdr, hout, fi);
-        e = hipGetLastError();
-    }
+    k_tile_scan<<<1, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa, hdr, hout, fi);
+    e = hipGetLastError();
     if (e != hipSuccess || !tile_cnt || !sa.sums) return e;
     const uint32_t nch = tile_scan_chunks(ntiles);
     k_tile_sums<<<nch, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa.chunk, sa.sums);
@@ -623,23 +624,6 @@ hipError_t launch_classify(hipStream_t s, const BatchDesc *desc, BatchDesc dv, u
 }
 
 uint32_t tile_scan_chunks(uint32_t ntiles) { return (ntiles + kScanChunk - 1) / kScanChunk; }
-
-// Last block of a scatter kernel to finish: clear the header for the next
-// batch.  Every block used its read of ERR before taking its ticket, so the
-// ticket needs no fence (a device-scope fence would write back L2).
-DEVI void scatter_done(uint32_t *hdr)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (__hip_atomic_fetch_add(&hdr[HDR_SCAT_DONE], 1u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
-            hdr[HDR_ERR] = 0;
-            hdr[HDR_NFLAG] = 0;
-            hdr[HDR_NFLAG_DEL] = 0;
-            hdr[HDR_SCAT_DONE] = 0;
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Direct scatter: every bucket change straight to HBM with device-scope
@@ -688,13 +672,12 @@ static uint32_t direct_blocks(uint32_t n, uint32_t C)
 
 __global__ __launch_bounds__(kDirThreads) void k_scatter_atomic(const BatchDesc *__restrict__ desc,
                                                                 BatchDesc dv, DevSketch sk,
-                                                                uint32_t *__restrict__ hdr)
+                                                                const uint32_t *__restrict__ hdr)
 {
-    const bool err = hdr[HDR_ERR] != 0;
+    const bool err = hdr[HDR_REJ] != 0;
     const uint32_t n = desc ? desc->n : dv.n;
     const uint64_t *upd = desc ? desc->upd : dv.upd;
     if (!err) scatter_direct(sk, upd, n);
-    scatter_done(hdr);
 }
 
 // ---------------------------------------------------------------------------
@@ -823,11 +806,10 @@ hipError_t launch_small_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, 
 }
 
 hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc dv,
-                                 uint32_t grid_n, DevSketch sk, uint32_t *hdr)
+                                 uint32_t grid_n, DevSketch sk, const uint32_t *hdr)
 {
     if (grid_n == 0) return hipSuccess;
-    // (a block's ticket in scatter_done is one atomic on one word)
-    const uint32_t grid = min(direct_blocks(grid_n, sk.C), 8u * kCus);
+    const uint32_t grid = min(direct_blocks(grid_n, sk.C), 16u * kCus);
     k_scatter_atomic<<<grid, kDirThreads, 0, s>>>(desc, dv, sk, hdr);
     return hipGetLastError();
 }
@@ -835,7 +817,7 @@ hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc
 // ---------------------------------------------------------------------------
 // Staged scatter.
 //
-// 1. tile scan (the last block of k_classify, once all counts are in):
+// 1. tile scan (one block, once all counts are in):
 //    exclusive scan of the per-tile record counts into bin offsets, and a
 //    list of work items (tile, chunk) where a chunk is at most `chunk`
 //    records of one tile's bin.
@@ -863,7 +845,7 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill(
     const uint32_t *__restrict__ hdr)
 {
     __shared__ uint32_t lcnt[kLdsHistMax];
-    if (hdr[HDR_ERR]) return;
+    if (hdr[HDR_REJ]) return;
     const uint64_t *__restrict__ upd = desc ? desc->upd : dv.upd;
     const uint32_t n = desc ? desc->n : dv.n;
     const uint32_t begin = blockIdx.x * kFillPerBlock;
@@ -944,7 +926,7 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill_staged(
     uint32_t *lcnt = (uint32_t *)(fsm + 2 * kFillPerBlock);  // per tile: count, then bin base
     uint32_t *lpre = lcnt + ntiles;                          // per tile: first stage slot
     uint32_t *sh = lpre + ntiles;                            // scan scratch (160 words)
-    if (hdr[HDR_ERR]) return;
+    if (hdr[HDR_REJ]) return;
     const uint64_t *__restrict__ upd = desc ? desc->upd : dv.upd;
     const uint32_t n = desc ? desc->n : dv.n;
     const uint32_t begin = blockIdx.x * kFillPerBlock;
@@ -1038,7 +1020,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_count(
     uint32_t fshift, uint32_t *__restrict__ cnt, const uint32_t *__restrict__ hdr)
 {
     __shared__ uint32_t hist[kFineLdsTiles];
-    if (hdr[HDR_ERR]) return;
+    if (hdr[HDR_REJ]) return;
     const uint32_t n = *total;
     const uint32_t begin = blockIdx.x * kFinePerBlock;
     if (begin >= n) return;
@@ -1078,7 +1060,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_fill(
     __shared__ uint32_t lcnt[kFillLdsTiles];    // per tile: count, then reserved bin start
     __shared__ uint32_t lpre[kFillLdsTiles];    // per tile: first stage slot
     __shared__ uint32_t sh[160];
-    if (hdr[HDR_ERR]) return;
+    if (hdr[HDR_REJ]) return;
     const uint32_t n = *total;
     const uint32_t begin = blockIdx.x * kFillPerBlock2;
     if (begin >= n) return;
@@ -1206,6 +1188,23 @@ DEVI uint32_t mix64_low(uint64_t z)
     return (uint32_t)z ^ __builtin_amdgcn_alignbit((uint32_t)(z >> 32), (uint32_t)z, 31);
 }
 
+// The buckets a block's threads changed, added to *touched (timed launches;
+// all threads of a block of at most 1,024, the same `touched`).  One atomic
+// per block: 4,000 of them on one word take 50 us.
+DEVI void add_touched(unsigned long long *touched, uint32_t t)
+{
+    if (!touched) return;
+    __shared__ uint32_t sum[16];
+#pragma unroll
+    for (uint32_t o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    if (__lane_id() == 0) sum[threadIdx.x / 64] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t w = 1; w < blockDim.x / 64; w++) t += sum[w];
+        if (t) atomicAdd(touched, (unsigned long long)t);
+    }
+}
+
 // f(integral_constant<uint32_t, T>) for T = 0 .. N-1
 template <uint32_t T, uint32_t N, class F>
 DEVI void static_for(F &&f)
@@ -1234,12 +1233,12 @@ template <uint32_t C>
 __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_stag(
     DevSketch sk, const uint64_t *__restrict__ bins, const uint32_t *__restrict__ off,
     const uint32_t *__restrict__ items, const uint32_t *__restrict__ nitems_p, uint32_t tile_shift,
-    uint32_t rows, uint32_t chunk, uint32_t *__restrict__ hdr,
+    uint32_t rows, uint32_t chunk, const uint32_t *__restrict__ hdr,
     unsigned long long *__restrict__ touched)
 {
     extern __shared__ uint64_t lds[];
     uint32_t nchanged = 0;  // buckets this thread changed in HBM
-    const bool err = hdr[HDR_ERR] != 0;
+    const bool err = hdr[HDR_REJ] != 0;
     const uint32_t TV = 1u << tile_shift;
     const uint32_t V = sk.V, D = sk.D;
     constexpr uint32_t RS = 2 * C;             // words per vertex and row: alpha, then gamma
@@ -1436,13 +1435,7 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
             }
         }
     }
-    if (touched) {
-        uint32_t t = nchanged;
-#pragma unroll
-        for (uint32_t o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-        if (lane == 0 && t) atomicAdd(touched, (unsigned long long)t);
-    }
-    scatter_done(hdr);
+    add_touched(touched, nchanged);
 }
 
 constexpr uint32_t kTileThreads = 512;
@@ -1522,13 +1515,13 @@ DEVI void tile_pair(uint8_t *lds8, uint32_t RSB, uint32_t pg, uint32_t rows, uin
 __global__ __launch_bounds__(kTileThreads) void k_tile_scatter(
     DevSketch sk, const uint64_t *__restrict__ bins, const uint32_t *__restrict__ off,
     const uint32_t *__restrict__ items, const uint32_t *__restrict__ nitems_p, uint32_t tile_shift,
-    uint32_t rows, uint32_t chunk, uint32_t *__restrict__ hdr,
+    uint32_t rows, uint32_t chunk, const uint32_t *__restrict__ hdr,
     unsigned long long *__restrict__ touched)
 {
     uint32_t nchanged = 0;  // buckets this thread changed in HBM
     extern __shared__ uint64_t lds[];
     uint8_t *lds8 = (uint8_t *)lds;
-    const bool err = hdr[HDR_ERR] != 0;
+    const bool err = hdr[HDR_REJ] != 0;
     const uint32_t TV = 1u << tile_shift;
     const uint32_t C = sk.C, V = sk.V;
     const uint32_t RS = TV * C;             // words per LDS depth row (< 2^12)
@@ -1628,13 +1621,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_scatter(
         }
         __syncthreads();
     }
-    if (touched) {
-        uint32_t t = nchanged;
-#pragma unroll
-        for (uint32_t o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-        if (__lane_id() == 0 && t) atomicAdd(touched, (unsigned long long)t);
-    }
-    scatter_done(hdr);
+    add_touched(touched, nchanged);
 }
 
 hipError_t launch_bin(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32_t grid_n,
@@ -1671,7 +1658,7 @@ static void for_columns(F &f)
     for_columns_impl(f, std::make_integer_sequence<uint32_t, kStagMaxC>{});
 }
 
-hipError_t launch_tile(hipStream_t s, DevSketch sk, uint32_t *hdr, const StagedParams &p,
+hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const StagedParams &p,
                        const uint32_t *tile_off, const uint64_t *bins, const uint32_t *items,
                        const uint32_t *nitems, unsigned long long *touched)
 {
@@ -1689,7 +1676,7 @@ hipError_t launch_tile(hipStream_t s, DevSketch sk, uint32_t *hdr, const StagedP
         // prefetching its next item (0.252 against 0.266 ms for 6.0e6
         // records on 200,003 vertices, 0.058 against 0.073 ms for 2.0e5 on
         // 131,072).
-        const uint32_t fit = kCus * max(1u, min(3u, (uint32_t)(kCuLds / lds)));
+        const uint32_t fit = kCus * max(1u, min(3u, (uint32_t)(kCuLds / (lds + 1280))));
         const uint32_t def = p.records >= (uint64_t)64 * sk.V ? 16 * kCus : fit;
         const uint32_t grid = min(p.items_cap, p.grid ? p.grid : def);
         hipError_t e = hipErrorInvalidValue;
@@ -1774,7 +1761,7 @@ __global__ __launch_bounds__(kReflagThreads) void k_reflag(uint32_t V, const uin
                                                            uint32_t *__restrict__ fdel, uint32_t nb)
 {
     const uint32_t b = blockIdx.x * (kReflagThreads / 64) + threadIdx.x / 64;
-    if (b >= nb || hdr[HDR_ERR] != 0) return;  // whole waves
+    if (b >= nb || hdr[HDR_REJ] != 0) return;  // whole waves
     const uint32_t lane = __lane_id();
     const uint32_t c = fcnt[b];
     uint64_t *r = fupd + (size_t)b * kClsPerBlock;
@@ -1825,8 +1812,10 @@ hipError_t launch_reflag(hipStream_t s, uint32_t V, const uint64_t *lp, uint32_t
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // header only: no tile counts
-    k_tile_scan<<<1, kScanThreads, 0, s>>>(nullptr, 0, ScanArgs{}, hdr, hout, fi);
+    // header only: no tile counts, and the verdict of the first scan
+    FlagInline f2 = fi;
+    f2.checked = 1;
+    k_tile_scan<<<1, kScanThreads, 0, s>>>(nullptr, 0, ScanArgs{}, hdr, hout, f2);
     return hipGetLastError();
 }
 

@@ -24,17 +24,19 @@ struct BatchDesc {
     uint32_t pad;
 };
 
-// Header words.  ERR / NFLAG / NFLAG_DEL are accumulated by the classify
-// kernel; SCAT_DONE counts finished blocks of the scatter kernel, whose last
-// block clears ERR / NFLAG / NFLAG_DEL (and SCAT_DONE) for the next batch.
-// SEQ counts published headers: the one-block kernel after classify copies
-// ERR / NFLAG / NFLAG_DEL to the host, then the incremented SEQ (release
-// store), which the host waits for.
+// Header words.  The classify kernel ORs ERR (a rejected batch); the
+// one-block kernel after it moves ERR to REJ, where the rest of the pass
+// reads it, and clears it for the next batch (the scatter leaves the header
+// alone: a ticket per block on one word took 12 ns each, 12 us behind a
+// launch of 1,024 blocks that finish together).  NFLAG and NFLAG_DEL exist
+// in the host copy only.  SEQ counts published headers: the one-block kernel
+// writes the verdict and the flag counts to the host, then the incremented
+// SEQ (release store), which the host waits for.
 enum {
     HDR_ERR = 0,
     HDR_NFLAG = 1,
     HDR_NFLAG_DEL = 2,
-    HDR_SCAT_DONE = 3,
+    HDR_REJ = 3,
     HDR_SEQ = 4,
     HDR_INLINE = 5,  // host copy only: the flagged updates came with the header
     HDR_WORDS = 8
@@ -56,6 +58,7 @@ struct FlagInline {
     // alone (launch_reflag checks the flags against a newer forest and
     // publishes them later); 0: it publishes them
     uint32_t tiles_only;
+    uint32_t checked;  // 1: ERR has been moved to REJ already (launch_reflag)
 };
 
 // Where the one-block tile scan writes: bin offsets and fill cursors
@@ -101,9 +104,9 @@ struct StagedParams {
 };
 
 // Per-batch: validation, structural classification and compaction of the
-// flagged updates.  hdr's ERR / NFLAG / NFLAG_DEL words must be zero (as
-// the previous batch's scatter leaves them).  A one-block kernel after it
-// writes their final values to `hout` (coherent pinned host memory,
+// flagged updates.  hdr's ERR word must be zero (as the one-block kernel of
+// the previous batch leaves it).  A one-block kernel after it writes the
+// verdict and the flag counts to `hout` (coherent pinned host memory,
 // HDR_WORDS words: no copy needed), then the next sequence number at
 // hout[HDR_SEQ].  When `tile_cnt` is non-null the classify kernel
 // also counts how many endpoint records each vertex tile gets, and the
@@ -190,22 +193,20 @@ hipError_t launch_small_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, 
                                 const uint32_t *derr);
 
 // Plain scatter: device-scope atomic XOR of (x, h) into both endpoints.
-// Its last block clears the header for the next batch.
 hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc dv,
-                                 uint32_t grid_n, DevSketch sk, uint32_t *hdr);
+                                 uint32_t grid_n, DevSketch sk, const uint32_t *hdr);
 
 // Staged scatter: launch_bin = fill of the per-tile bins (at the offsets
 // the classify kernel's tile scan wrote: the count copy's start in
 // tile_goff plus the classify block's tile_rel entry when tile_rel is
 // non-null, else reserved from tile_cur);
-// launch_tile = LDS-staged XOR per work item, whose last block clears the
-// header for the next batch; touched (may be null) is incremented by the
-// number of buckets the launch changes in HBM.
+// launch_tile = LDS-staged XOR per work item; touched (may be null) is
+// incremented by the number of buckets the launch changes in HBM.
 hipError_t launch_bin(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32_t grid_n,
                       DevSketch sk, const uint32_t *hdr, const StagedParams &p,
                       uint32_t *tile_cur, uint64_t *bins, const uint32_t *tile_goff,
                       const uint32_t *tile_rel);
-hipError_t launch_tile(hipStream_t s, DevSketch sk, uint32_t *hdr, const StagedParams &p,
+hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const StagedParams &p,
                        const uint32_t *tile_off, const uint64_t *bins, const uint32_t *items,
                        const uint32_t *nitems, unsigned long long *touched);
 // Second level of the two-level binning (used when there are more tiles
