@@ -944,9 +944,11 @@ static FlagInline flag_inline(cupk_ctx *ctx, uint32_t grid_n)
 
 // tiles_only: leave the flags unpublished (an overlapped pass checks them
 // again against the forest after the previous batch's rounds).
-int enqueue_classify(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n, bool tiles_only = false)
+// direct: no tile counts (a direct scatter follows).
+int enqueue_classify(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n, bool tiles_only = false,
+                     bool direct = false)
 {
-    const bool staged = ctx->opts.scatter_mode == CUPK_SCATTER_STAGED;
+    const bool staged = ctx->opts.scatter_mode == CUPK_SCATTER_STAGED && !direct;
     ScanArgs sa = {};
     if (staged) {
         sa.off = ctx->d_toff.p;
@@ -1160,6 +1162,28 @@ static int enqueue_split_back(cupk_ctx *ctx, uint32_t n)
     return CUPK_OK;
 }
 
+// Whether a batch of n > kSmallMax updates goes to HBM directly (one device
+// atomic per changed word) instead of through the tiles.  The direct pass
+// costs about 14 us and 52 ps per (update, column); the staged one a chain of
+// short kernels and the lines of the touched vertices, which grow with V
+// (classification included, us, direct / staged): V = 16,384: 22 / 33 at
+// 10,000 updates, 44 / 37 at 40,000; 65,536: 31 / 71 at 20,000, 76 / 78 at
+// 80,000; 131,072: 85 / 100 at 80,000, 156 / 125 at 160,000; 2^20: 94 / 308
+// at 80,000.  Uniform batches break even near 380K, 1.3M and 1.8M pairs (at
+// V = 1,024 near 170K).  The line is drawn lower because updates that share a
+// vertex serialize on its words (17 ns each; k_mid_scatter takes the edge off):
+// with one vertex in a tenth of 8,000 updates on 16,384 vertices both take
+// 33 us.  A caller that sets the tile geometry gets the tiles.
+static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
+{
+    if (ctx->opts.scatter_mode != CUPK_SCATTER_STAGED) return true;
+    const cupk_opts &o = ctx->opts;
+    if (o.tile_vertices || o.lds_rows || o.chunk_records || o.tile_grid || o.fill_reserve ||
+        o.tile_layout || o.coarse_tiles)
+        return false;
+    return (uint64_t)n * ctx->C <= std::max<uint64_t>(100000, 8 * (uint64_t)ctx->V);
+}
+
 int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert)
 {
     int rc = harvest_timers(ctx, false);
@@ -1170,20 +1194,25 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert)
         if (rc != CUPK_OK) return rc;
     }
     const bool graph = ctx->opts.use_graph != 0 && !ctx->opts.exact;
-    ctx->small_pass = !graph && n <= kSmallMax;
+    const bool direct = !graph && n > kSmallMax && direct_pays(ctx, n);
+    // (timed contexts time every pass beyond kSmallMax)
+    ctx->small_pass = !graph && (n <= kSmallMax ||
+                                 (direct && n <= kOneBlockMax && !ctx->opts.time_kernels));
     if (ctx->small_pass) {
         // two launches and one copy: classify into the result block, copy
         // header + flags + positions to the host, scatter with device
         // atomics (the previous small result was read before this pass:
         // every pass waits for its header or for the whole stream)
         uint32_t *derr = &ctx->d_small->hdr[HDR_ERR];
-        HIPCHK(launch_small_classify(ctx->s, d_upd, n, ctx->V, ctx->d_lbl, ctx->d_par,
-                                     ctx->h_small, derr, ctx->d_hdr + HDR_SEQ,
-                                     ctx->opts.exact != 0));
+        HIPCHK(launch_small_classify(ctx->s, d_upd, n, ctx->V, ctx->d_lp, ctx->h_small, derr,
+                                     ctx->d_hdr + HDR_SEQ, ctx->opts.exact != 0));
         ctx->hdr_seq++;
         ctx->hdr_word = &ctx->h_small->hdr[HDR_SEQ];
         // the host walks the flags while the scatter runs
-        HIPCHK(launch_small_scatter(ctx->s, d_upd, n, dev_sketch(ctx), derr));
+        if (n <= kSmallMax)
+            HIPCHK(launch_small_scatter(ctx->s, d_upd, n, dev_sketch(ctx), derr));
+        else
+            HIPCHK(launch_mid_scatter(ctx->s, d_upd, n, dev_sketch(ctx), derr, nullptr));
         ctx->ctr.scatter_launches++;
         return CUPK_OK;
     }
@@ -1223,13 +1252,18 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert)
         HIPCHK(hipGraphLaunch(ctx->gx_tile, ctx->s));
     } else {
         // scatter skipped on the device if the batch was rejected
-        rc = enqueue_classify(ctx, ctx->s, n);
+        const bool staged = ctx->opts.scatter_mode == CUPK_SCATTER_STAGED;
+        rc = enqueue_classify(ctx, ctx->s, n, false, direct);
         if (rc != CUPK_OK) return rc;
         if (ts) HIPCHK(hipEventRecord(ts->t0, ctx->s));
-        rc = enqueue_bin(ctx, ctx->s, n);
+        if (!direct) rc = enqueue_bin(ctx, ctx->s, n);
         if (rc != CUPK_OK) return rc;
         if (ts) HIPCHK(hipEventRecord(ts->tb, ctx->s));
-        rc = enqueue_tile(ctx, ctx->s, n, ts != nullptr);
+        if (direct && staged)
+            HIPCHK(launch_mid_scatter(ctx->s, d_upd, n, dev_sketch(ctx), ctx->d_hdr + HDR_REJ,
+                                      ts ? ctx->d_touched : nullptr));
+        else
+            rc = enqueue_tile(ctx, ctx->s, n, ts != nullptr);
         if (rc != CUPK_OK) return rc;
     }
     ctx->hdr_seq++;

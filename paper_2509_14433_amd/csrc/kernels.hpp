@@ -172,25 +172,33 @@ hipError_t launch_flag_compact(hipStream_t s, uint32_t n, const uint64_t *fupd,
                                uint64_t *oupd, uint32_t *opos);
 
 // Small batches: header, flagged updates (stream order) and their positions
-// of one batch of at most kSmallMax updates, written by one kernel straight
-// into host memory.
+// of one batch of at most kOneBlockMax updates, written by one kernel straight
+// into host memory.  Batches of at most kSmallMax updates always go this way;
+// up to kOneBlockMax those that the direct scatter suits (direct_pays in
+// api.cpp).
 constexpr uint32_t kSmallMax = 4096;
+constexpr uint32_t kOneBlockMax = 16384;
 struct SmallResult {
     uint32_t hdr[HDR_WORDS];
-    uint64_t fupd[kSmallMax];
-    uint32_t fpos[kSmallMax];
+    uint64_t fupd[kOneBlockMax];
+    uint32_t fpos[kOneBlockMax];
 };
-// Classify (one block) a batch of 1..kSmallMax packed updates given in the
+// Classify (one block) a batch of 1..kOneBlockMax packed updates given in the
 // arguments into `out` (coherent pinned host memory; with_pos: also
 // positions), set *derr (device) to the error flag, and publish the next
 // value of the counter *seqp at out->hdr[HDR_SEQ] (release store) once the
-// rest of `out` is written.  Then scatter it with device atomics; the
-// scatter does nothing if an update was invalid (*derr set).
+// rest of `out` is written.
 hipError_t launch_small_classify(hipStream_t s, const uint64_t *upd, uint32_t n, uint32_t V,
-                                 const uint32_t *lbl, const uint32_t *par, SmallResult *out,
-                                 uint32_t *derr, uint32_t *seqp, bool with_pos);
+                                 const uint64_t *lp, SmallResult *out, uint32_t *derr,
+                                 uint32_t *seqp, bool with_pos);
+// Direct scatters, with device atomics, of a classified batch; they do nothing
+// if an update was invalid (*derr set).  Small: at most kSmallMax updates.
+// Mid: any number; a vertex that takes a large share of the batch is gathered
+// per block; touched as for launch_tile.
 hipError_t launch_small_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, DevSketch sk,
                                 const uint32_t *derr);
+hipError_t launch_mid_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, DevSketch sk,
+                              const uint32_t *derr, unsigned long long *touched);
 
 // Plain scatter: device-scope atomic XOR of (x, h) into both endpoints.
 hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc dv,
