@@ -153,13 +153,54 @@ struct RoundSet {
     uint8_t kind = 0;  // reduced from: 0 vertices, 1 fragments, 2 the other fragments
 };
 
-// Reduce k sets into d_sig[slot] (internal layout, W words per set) and
-// sample them into h_res.  Vertex sets come as (members, offsets) over
-// vertex ids; fragment sets as (members, offsets) over slots of
-// d_sig[1-slot].  Set order: vertex sets first, then fragment sets.
-int reduce_and_sample(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vmem,
-                      const std::vector<uint32_t> &voff, const std::vector<uint32_t> &fmem,
-                      const std::vector<uint32_t> &foff)
+// Wait until a kernel of stream st has published `seq` at the host word w.
+// The stream is queried now and then: if it has drained and the number is
+// still missing, or it reports an error, the wait fails instead of spinning
+// on.  every: milliseconds between queries (0: every 256 spins); a query of a
+// busy stream can queue a marker, which idles the GPU for a few microseconds
+// between two kernels.
+static int wait_word(cupk_ctx *ctx, const uint32_t *w, uint32_t seq, hipStream_t st, double every)
+{
+    double next_query = 0;
+    for (uint32_t spin = 1;; spin++) {
+        if (__atomic_load_n(w, __ATOMIC_ACQUIRE) == seq) return CUPK_OK;
+        if ((spin & 255) == 0) {
+            const double t = now_ms();
+            if (next_query == 0) next_query = t + every;
+            if (t < next_query) {
+                __builtin_ia32_pause();
+                continue;
+            }
+            next_query = t + every;
+            const hipError_t e = hipStreamQuery(st);
+            if (e == hipSuccess) {
+                if (__atomic_load_n(w, __ATOMIC_ACQUIRE) == seq) return CUPK_OK;
+                return ctx->fail(hipErrorUnknown, "a result was not published", __LINE__);
+            }
+            if (e != hipErrorNotReady) return ctx->fail(e, "hipStreamQuery", __LINE__);
+        }
+        __builtin_ia32_pause();
+    }
+}
+
+// Members and work items up to this many words are read by the kernel from
+// pinned host memory, and the results of up to kDirectSets sets written
+// there; beyond, copies are faster.
+constexpr size_t kDirectWords = 1u << 16;
+constexpr uint32_t kDirectSets = 4096;
+// Sketches up to this many bytes pass between host arrays and kernels through
+// a pinned block that the kernel reads or writes itself.
+constexpr size_t kDirectBytes = (size_t)256 << 10;
+
+// Reduce k sets and wait for the results: with `query`, into d_sig[slot]
+// (internal layout, W words per set) and each queried into h_res; else, into
+// `canon` (canonical order, device or pinned host memory).  Vertex sets come
+// as (members, offsets) over vertex ids; fragment sets as (members, offsets)
+// over slots of d_sig[1-slot].  Set order: vertex sets first, then fragment
+// sets.
+static int reduce_sets(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vmem,
+                       const std::vector<uint32_t> &voff, const std::vector<uint32_t> &fmem,
+                       const std::vector<uint32_t> &foff, bool query, uint64_t *canon)
 {
     const uint32_t kv = voff.empty() ? 0 : (uint32_t)voff.size() - 1;
     const uint32_t kf = foff.empty() ? 0 : (uint32_t)foff.size() - 1;
@@ -167,51 +208,92 @@ int reduce_and_sample(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vmem
     if (k == 0) return CUPK_OK;
     const uint32_t W = ctx->W;
     const hipStream_t rs = ctx->rstream;
-    HIPCHK(grow(ctx->d_sig[slot], (size_t)k * W));
-    HIPCHK(grow(ctx->d_res, (size_t)3 * k));
-    HIPCHK(grow(ctx->h_res, (size_t)3 * k));
-    // work items
-    std::vector<uint32_t> items;
-    auto add_items = [&](const std::vector<uint32_t> &off, uint32_t set0, uint32_t mem0) {
-        for (size_t j = 0; j + 1 < off.size(); j++)
-            for (uint32_t b = off[j]; b < off[j + 1]; b += kRedChunk) {
-                items.push_back(set0 + (uint32_t)j);
-                items.push_back(mem0 + b);
-                items.push_back(mem0 + std::min(off[j + 1], b + kRedChunk));
-            }
-    };
-    add_items(voff, 0, 0);
-    const size_t nvi = items.size() / 3;
-    add_items(foff, kv, (uint32_t)vmem.size());
-    const size_t nitems = items.size() / 3;
-    // members, then the work items, in one buffer and one copy
     const size_t nmem = vmem.size() + fmem.size();
-    const size_t nall = nmem + items.size();
-    HIPCHK(grow(ctx->h_ridx, nall + 1));
-    HIPCHK(grow(ctx->d_ridx, nall + 1));
-    std::copy(vmem.begin(), vmem.end(), ctx->h_ridx.p);
-    std::copy(fmem.begin(), fmem.end(), ctx->h_ridx.p + vmem.size());
-    std::copy(items.begin(), items.end(), ctx->h_ridx.p + nmem);
-    if (nall)
-        HIPCHK(hipMemcpyAsync(ctx->d_ridx.p, ctx->h_ridx.p, nall * 4, hipMemcpyHostToDevice,
-                              rs));
-    const uint32_t *d_items = ctx->d_ridx.p + nmem;
-    uint64_t *sig = ctx->d_sig[slot].p;
-    HIPCHK(launch_zero(rs, sig, (size_t)k * W));
-    if (nvi)
-        HIPCHK(launch_reduce(rs, ctx->d_sk, W, ctx->d_ridx.p, d_items, (uint32_t)nvi,
-                             sig));
-    if (nitems > nvi)
-        HIPCHK(launch_reduce(rs, ctx->d_sig[1 - slot].p, W, ctx->d_ridx.p,
-                             d_items + 3 * nvi, (uint32_t)(nitems - nvi), sig));
-    HIPCHK(launch_sample(rs, sig, k, ctx->V, ctx->C, ctx->D, 1, ctx->C, W, ctx->d_seeds,
-                         ctx->d_res.p));
-    HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, (size_t)3 * k * 4, hipMemcpyDeviceToHost,
-                          rs));
-    HIPCHK(hipStreamSynchronize(rs));
+    const uint32_t chunk = kRedChunk;
+    size_t nitems = 0, nzero = 0;
+    auto parts_of = [&](uint32_t n) { return n <= chunk ? 1u : (n + chunk - 1) / chunk; };
+    auto count = [&](const std::vector<uint32_t> &off) {
+        for (size_t j = 0; j + 1 < off.size(); j++) {
+            const uint32_t p = parts_of(off[j + 1] - off[j]);
+            nitems += p;
+            nzero += p > 1;
+        }
+    };
+    count(voff);
+    count(foff);
+    // members, work items and the sets to zero, in one buffer
+    const size_t nall = nmem + 4 * nitems + nzero;
+    const bool direct = nall <= kDirectWords;
+    HIPCHK(grow(ctx->h_ridx, nall + 1, hipHostMallocCoherent));
+    if (!direct) HIPCHK(grow(ctx->d_ridx, nall + 1));
+    if (query || nzero) HIPCHK(grow(ctx->d_sig[slot], (size_t)k * W));
+    if (nzero) HIPCHK(grow(ctx->d_tick, k));
+    uint32_t *h = ctx->h_ridx.p;
+    std::copy(vmem.begin(), vmem.end(), h);
+    std::copy(fmem.begin(), fmem.end(), h + vmem.size());
+    uint32_t *it = h + nmem, *zl = it + 4 * nitems;
+    auto fill = [&](const std::vector<uint32_t> &off, uint32_t set0, uint32_t mem0, uint32_t bit) {
+        for (size_t j = 0; j + 1 < off.size(); j++) {
+            const uint32_t n = off[j + 1] - off[j], p = parts_of(n), set = set0 + (uint32_t)j;
+            if (p > 1) *zl++ = set;
+            for (uint32_t q = 0; q < p; q++, it += 4) {
+                it[0] = set | bit;
+                it[1] = mem0 + off[j] + q * chunk;
+                it[2] = mem0 + std::min(off[j + 1], off[j] + (q + 1) * chunk);
+                it[3] = p;
+            }
+        }
+    };
+    fill(voff, 0, 0, 0);
+    fill(foff, kv, (uint32_t)vmem.size(), 1u << 31);
+    const uint32_t *base = h;
+    if (!direct) {
+        HIPCHK(hipMemcpyAsync(ctx->d_ridx.p, h, nall * 4, hipMemcpyHostToDevice, rs));
+        base = ctx->d_ridx.p;
+    }
+    const bool pub = !query || k <= kDirectSets;
+    if (query) {
+        HIPCHK(grow(ctx->h_res, (size_t)3 * k, hipHostMallocCoherent));
+        if (!pub) HIPCHK(grow(ctx->d_res, (size_t)3 * k));
+    }
+    ReduceArgs a = {};
+    a.src0 = ctx->d_sk;
+    a.src1 = ctx->d_sig[1 - slot].p;
+    a.items = base + nmem;
+    a.idx = base;
+    a.nitems = (uint32_t)nitems;
+    a.members = (uint32_t)nmem;
+    a.V = ctx->V;
+    a.C = ctx->C;
+    a.D = ctx->D;
+    a.seeds = ctx->d_seeds;
+    a.sig = query || nzero ? ctx->d_sig[slot].p : nullptr;
+    a.tick = ctx->d_tick.p;
+    a.canon = query ? nullptr : canon;
+    a.res = !query ? nullptr : pub ? ctx->h_res.p : ctx->d_res.p;
+    if (pub) {
+        a.seq_out = ctx->h_pub;
+        a.seq = ++ctx->pub_seq;
+    }
+    HIPCHK(launch_reduce_sample(rs, a, base + nmem + 4 * nitems, (uint32_t)nzero));
+    if (pub) {
+        const int rc = wait_word(ctx, ctx->h_pub, a.seq, rs, 1.0);
+        if (rc != CUPK_OK) return rc;
+    } else {
+        HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, (size_t)3 * k * 4,
+                              hipMemcpyDeviceToHost, rs));
+        HIPCHK(hipStreamSynchronize(rs));
+    }
     ctx->ctr.sets_reduced += k;
     ctx->ctr.slabs_reduced += nmem;
     return CUPK_OK;
+}
+
+int reduce_and_sample(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vmem,
+                      const std::vector<uint32_t> &voff, const std::vector<uint32_t> &fmem,
+                      const std::vector<uint32_t> &foff)
+{
+    return reduce_sets(ctx, slot, vmem, voff, fmem, foff, true, nullptr);
 }
 
 // First replacement round over the pieces of the trees that pending
@@ -1304,39 +1386,13 @@ int walk_exact(cupk_ctx *ctx, const uint64_t *upd, uint32_t k0, uint32_t k1, boo
 }
 
 // Wait until the header with sequence number `seq` has been published to
-// host memory.  The stream is queried now and then: if it has drained and
-// the header is still missing, or it reports an error, the wait fails
-// instead of spinning on.
-// A batch already in device memory: the stream is queried only after a
-// millisecond without the header, then once per millisecond (a query of a
-// busy stream can queue a marker, which idles the GPU for a few
-// microseconds between two kernels).  A batch uploaded from host memory:
-// every 256 spins, which kept the served query latency lower.
+// host memory.  A batch already in device memory: the stream is queried only
+// after a millisecond without the header, then once per millisecond.  A batch
+// uploaded from host memory: every 256 spins, which kept the served query
+// latency lower.
 static int wait_header(cupk_ctx *ctx, uint32_t seq)
 {
-    uint32_t *w = ctx->hdr_word;
-    const double every = ctx->query_often ? 0.0 : 1.0;
-    double next_query = 0;
-    for (uint32_t spin = 1;; spin++) {
-        if (__atomic_load_n(w, __ATOMIC_ACQUIRE) == seq) return CUPK_OK;
-        if ((spin & 255) == 0) {
-            const double t = now_ms();
-            if (next_query == 0) next_query = t + every;
-            if (t < next_query) {
-                __builtin_ia32_pause();
-                continue;
-            }
-            next_query = t + every;
-            const hipError_t e = hipStreamQuery(ctx->s);
-            if (e == hipSuccess) {
-                if (__atomic_load_n(w, __ATOMIC_ACQUIRE) == seq) return CUPK_OK;
-                return ctx->fail(hipErrorUnknown, "classification header was not published",
-                                 __LINE__);
-            }
-            if (e != hipErrorNotReady) return ctx->fail(e, "hipStreamQuery", __LINE__);
-        }
-        __builtin_ia32_pause();
-    }
+    return wait_word(ctx, ctx->hdr_word, seq, ctx->s, ctx->query_often ? 0.0 : 1.0);
 }
 
 // Host side of a pass: wait for the classification header, pack and fetch
@@ -1600,8 +1656,6 @@ static int apply_flushed(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool 
             rc = enqueue_pass(ctx, d_upd + next, n - next, true);
             if (rc != CUPK_OK) return rc;
             ctx->ctr.reverts++;
-            // the descriptor staging is written again by the next pass
-            HIPCHK(hipStreamSynchronize(ctx->s));
         }
         ctx->forest.cut(a, b);
         ctx->ctr.cuts++;
@@ -1659,6 +1713,7 @@ void destroy(cupk_ctx *ctx)
     if (ctx->d_small) (void)hipFree(ctx->d_small);
     if (ctx->h_small) (void)hipHostFree(ctx->h_small);
     if (ctx->h_misc) (void)hipHostFree(ctx->h_misc);
+    if (ctx->h_pub) (void)hipHostFree(ctx->h_pub);
     release(ctx->d_upd);
     release(ctx->h_upd);
     release(ctx->d_fupd);
@@ -1688,8 +1743,10 @@ void destroy(cupk_ctx *ctx)
     release(ctx->h_ridx);
     release(ctx->d_sig[0]);
     release(ctx->d_sig[1]);
+    release(ctx->d_tick);
     release(ctx->d_res);
     release(ctx->h_res);
+    release(ctx->h_canon);
     release(ctx->d_tmp);
     release(ctx->h_stage);
     release(ctx->d_stage);
@@ -1862,6 +1919,8 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     HIPCHK(hipHostMalloc((void **)&ctx->h_small, sizeof(SmallResult), hipHostMallocCoherent));
     memset(ctx->h_small, 0, sizeof(SmallResult));
     HIPCHK(hipHostMalloc((void **)&ctx->h_misc, 64, hipHostMallocDefault));
+    HIPCHK(hipHostMalloc((void **)&ctx->h_pub, 64, hipHostMallocCoherent));
+    memset(ctx->h_pub, 0, 64);
     ctx->forest.init(V, ctx->h_lbl, ctx->h_par);
     ctx->forest.track_pages(10);  // 4 KiB of labels (and of parents) per page
     if (V >= (1u << 17)) {
@@ -1919,10 +1978,10 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
         const size_t items = V / kRedChunk + sets + 1;
         HIPCHK(grow(ctx->d_sig[0], sets * ctx->W));
         HIPCHK(grow(ctx->d_sig[1], sets * ctx->W));
-        HIPCHK(grow(ctx->d_res, 3 * sets));
-        HIPCHK(grow(ctx->h_res, 3 * sets));
-        HIPCHK(grow(ctx->d_ridx, (size_t)V + 1 + 3 * items));
-        HIPCHK(grow(ctx->h_ridx, (size_t)V + 1 + 3 * items));
+        HIPCHK(grow(ctx->d_tick, sets));
+        HIPCHK(grow(ctx->h_res, 3 * sets, hipHostMallocCoherent));
+        HIPCHK(grow(ctx->d_ridx, (size_t)V + 1 + 4 * items + sets));
+        HIPCHK(grow(ctx->h_ridx, (size_t)V + 1 + 4 * items + sets, hipHostMallocCoherent));
     }
     HIPCHK(hipStreamSynchronize(ctx->s));
     return CUPK_OK;
@@ -2064,17 +2123,26 @@ int cupk_component_sketch_batch(cupk_ctx *ctx, const uint64_t *offsets, size_t k
             if (verts[i] >= ctx->V) return ctx->invalid("vertex id >= V");
         std::vector<uint32_t> vmem(verts, verts + nv), voff(k + 1), none;
         for (size_t j = 0; j <= k; j++) voff[j] = (uint32_t)offsets[j];
-        int rc = reduce_and_sample(ctx, 0, vmem, voff, none, none);
-        if (rc != CUPK_OK) return rc;
-        if (is_device_ptr(out)) {
-            HIPCHK(launch_to_canonical(ctx->s, ctx->d_sig[0].p, ctx->C, ctx->D, k,
-                                       (uint64_t *)out));
-        } else {
-            HIPCHK(grow(ctx->d_tmp, (size_t)k * ctx->W));
-            HIPCHK(launch_to_canonical(ctx->s, ctx->d_sig[0].p, ctx->C, ctx->D, k, ctx->d_tmp.p));
-            HIPCHK(hipMemcpyAsync(out, ctx->d_tmp.p, (size_t)k * ctx->W * 8,
-                                  hipMemcpyDeviceToHost, ctx->s));
+        const size_t words = (size_t)k * ctx->W;
+        // the kernel writes canonical order itself: to the caller's device
+        // memory, to a pinned block (copied out by the host), or, for large
+        // results, to a device buffer
+        uint64_t *canon = (uint64_t *)out;
+        const bool dev = is_device_ptr(out), small = words * 8 <= kDirectBytes;
+        if (!dev && small) {
+            HIPCHK(grow(ctx->h_canon, words, hipHostMallocCoherent));
+            canon = ctx->h_canon.p;
+        } else if (!dev) {
+            HIPCHK(grow(ctx->d_tmp, words));
+            canon = ctx->d_tmp.p;
         }
+        const int rc = reduce_sets(ctx, 0, vmem, voff, none, none, false, canon);
+        if (rc != CUPK_OK || dev) return rc;
+        if (small) {
+            memcpy(out, canon, words * 8);
+            return CUPK_OK;
+        }
+        HIPCHK(hipMemcpyAsync(out, canon, words * 8, hipMemcpyDeviceToHost, ctx->s));
         HIPCHK(hipStreamSynchronize(ctx->s));
         return CUPK_OK;
     });
@@ -2138,15 +2206,34 @@ int cupk_sample_cut_edge_batch(cupk_ctx *ctx, const cupk_bucket *sketches, size_
         if (!sketches || !status || !u || !v) return ctx->invalid("null array");
         if (k >= (1ull << 31)) return ctx->invalid("too many sketches");
         const size_t words = (size_t)k * ctx->W;
-        HIPCHK(grow(ctx->d_tmp, words));
-        HIPCHK(grow(ctx->d_res, 3 * k));
-        HIPCHK(grow(ctx->h_res, 3 * k));
-        HIPCHK(hipMemcpyAsync(ctx->d_tmp.p, sketches, words * 8, hipMemcpyHostToDevice, ctx->s));
-        // canonical layout: bucket (c, d) at word (c*D + d)*2
-        HIPCHK(launch_sample(ctx->s, ctx->d_tmp.p, (uint32_t)k, ctx->V, ctx->C, ctx->D, ctx->D, 1,
-                             ctx->W, ctx->d_seeds, ctx->d_res.p));
-        HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, 3 * k * 4, hipMemcpyDeviceToHost, ctx->s));
-        HIPCHK(hipStreamSynchronize(ctx->s));
+        // few sketches: the kernel reads them from a pinned block, and writes
+        // its results to pinned memory
+        const uint64_t *src;
+        if (words * 8 <= kDirectBytes) {
+            HIPCHK(grow(ctx->h_canon, words, hipHostMallocCoherent));
+            memcpy(ctx->h_canon.p, sketches, words * 8);
+            src = ctx->h_canon.p;
+        } else {
+            HIPCHK(grow(ctx->d_tmp, words));
+            HIPCHK(hipMemcpyAsync(ctx->d_tmp.p, sketches, words * 8, hipMemcpyHostToDevice,
+                                  ctx->s));
+            src = ctx->d_tmp.p;
+        }
+        HIPCHK(grow(ctx->h_res, 3 * k, hipHostMallocCoherent));
+        if (k <= kDirectSets) {
+            const uint32_t seq = ++ctx->pub_seq;
+            HIPCHK(launch_sample(ctx->s, src, (uint32_t)k, ctx->V, ctx->C, ctx->D, ctx->d_seeds,
+                                 ctx->h_res.p, ctx->h_pub, seq));
+            const int rc = wait_word(ctx, ctx->h_pub, seq, ctx->s, 1.0);
+            if (rc != CUPK_OK) return rc;
+        } else {
+            HIPCHK(grow(ctx->d_res, 3 * k));
+            HIPCHK(launch_sample(ctx->s, src, (uint32_t)k, ctx->V, ctx->C, ctx->D, ctx->d_seeds,
+                                 ctx->d_res.p, nullptr, 0));
+            HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, 3 * k * 4, hipMemcpyDeviceToHost,
+                                  ctx->s));
+            HIPCHK(hipStreamSynchronize(ctx->s));
+        }
         for (size_t j = 0; j < k; j++) {
             status[j] = ctx->h_res.p[3 * j];
             u[j] = (uint32_t)ctx->h_res.p[3 * j + 1];
@@ -2344,7 +2431,7 @@ static int time_scatter(cupk_ctx *ctx, const uint64_t *d, uint32_t n, int reps, 
 static int static_components(cupk_ctx *ctx, uint32_t *labels, uint32_t *eu, uint32_t *ev,
                              cupk_static_info *info)
 {
-    const uint32_t V = ctx->V, W = ctx->W;
+    const uint32_t V = ctx->V;
     std::vector<uint32_t> parent(V), size(V, 1);
     for (uint32_t w = 0; w < V; w++) parent[w] = w;
     auto find = [&](uint32_t x) {
@@ -2371,9 +2458,16 @@ static int static_components(cupk_ctx *ctx, uint32_t *labels, uint32_t *eu, uint
             set_size.assign(V, 1);
             for (uint32_t w = 0; w < V; w++) set_min[w] = w;
             HIPCHK(grow(ctx->d_res, (size_t)3 * V));
-            HIPCHK(grow(ctx->h_res, (size_t)3 * V));
-            HIPCHK(launch_sample(ctx->s, ctx->d_sk, V, V, ctx->C, ctx->D, 1, ctx->C, W,
-                                 ctx->d_seeds, ctx->d_res.p));
+            HIPCHK(grow(ctx->h_res, (size_t)3 * V, hipHostMallocCoherent));
+            ReduceArgs a = {};  // item i: vertex i alone
+            a.src0 = ctx->d_sk;
+            a.nitems = V;
+            a.V = V;
+            a.C = ctx->C;
+            a.D = ctx->D;
+            a.seeds = ctx->d_seeds;
+            a.res = ctx->d_res.p;
+            HIPCHK(launch_reduce_sample(ctx->s, a, nullptr, 0));
             HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, (size_t)3 * V * 4,
                                   hipMemcpyDeviceToHost, ctx->s));
             HIPCHK(hipStreamSynchronize(ctx->s));

@@ -22,7 +22,7 @@
 
 namespace cupk {
 
-constexpr uint32_t kRedChunk = 16;          // members per reduction work item
+constexpr uint32_t kColChunk = 16;          // members per one-column reduction work item
 constexpr size_t kMaxBatchPerLaunch = 1u << 28;
 constexpr int kTimerRing = 64;
 
@@ -120,6 +120,10 @@ struct cupk_ctx {
     cupk::DevBuf<uint32_t> d_ridx;   // members, then the work items, of a reduction
     cupk::HostBuf<uint32_t> h_ridx;
     cupk::DevBuf<uint64_t> d_sig[2];
+    cupk::DevBuf<uint32_t> d_tick;   // tickets of sets reduced by several items
+    cupk::HostBuf<uint64_t> h_canon; // sketches on their way between host arrays and kernels
+    uint32_t *h_pub = nullptr;       // where reductions and queries publish that they are done
+    uint32_t pub_seq = 0;            // numbers published there so far (expected)
     cupk::DevBuf<int32_t> d_res;
     cupk::HostBuf<int32_t> h_res;
     cupk::DevBuf<uint64_t> d_tmp;

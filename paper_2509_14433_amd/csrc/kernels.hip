@@ -21,6 +21,9 @@ namespace cupk {
 constexpr uint32_t kCus = 256;
 constexpr size_t kCuLds = 163840;  // LDS per CU, bytes
 
+// two words of a bucket; the caller's sketch memory may be 8-byte aligned
+typedef uint64_t Bucket2 __attribute__((ext_vector_type(2), aligned(8)));
+
 // SplitMix64 output finalizer (Steele, Lea, Flood 2014).
 DEVI uint64_t mix64(uint64_t z)
 {
@@ -1287,9 +1290,6 @@ hipError_t launch_fine(hipStream_t s, uint32_t grid_n, const uint32_t *hdr, cons
 //   2.0e5 on 131,072, C = 17:                 0.058 / 0.073 / 0.084 ms
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) uint64_t *LdsWords;
-// two words of a bucket; the caller's sketch memory may be 8-byte aligned
-typedef uint64_t Bucket2 __attribute__((ext_vector_type(2), aligned(8)));
-
 DEVI void lds_xor(LdsWords p, uint64_t v)
 {
     __hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1958,73 +1958,271 @@ hipError_t launch_zero32(hipStream_t s, uint32_t *p, size_t n)
 }
 
 // ---------------------------------------------------------------------------
-// Segmented XOR reduction (component sketches).  A work item is
-// (set, begin, end) over the member list; the block streams the members'
-// slabs (W words each, coalesced across lanes) and XORs them into
-// registers, then folds the nonzero words into out[set] with device
-// atomics (a set may span several work items).
+// Segmented XOR reduction (component sketches) with the query of every set in
+// the same launch.  A work item is (set, begin, end, items of the set), at
+// most kRedChunk members of one set.  A block takes an item: NG groups of 256
+// threads stream every NG-th member's slab, one 16-byte bucket per lane and
+// load, several members' loads in flight, XOR them into registers and add up
+// in LDS.  A set of one item is then queried from registers.  A set of
+// several items adds up in its aggregate with device atomics; the block that
+// takes the set's last ticket reads it back and queries it.
+//
+// Query of an aggregate: every lane checks its buckets (alpha != 0, checksum
+// and depth derived again from alpha, alpha decodes to u < v < V), the block
+// takes the minimum canonical rank c*D + (D-1-d) among the good ones, and the
+// lane that holds it writes the edge; an OR over all words tells EMPTY.
+//
+// Large sets are bound by HBM (the slabs read once); small ones by latency,
+// hence one launch where there were a zero fill, a reduction, a query and a
+// copy in either direction: members and items come from pinned host memory
+// when they are few, results go there, and a lone item publishes them itself.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kRedThreads = 256;
+constexpr uint32_t kRedThreads = 256;  // per group
 
-// KMAX words per lane: slabs of up to KMAX*256 words (C*D*2 <= KMAX*256).
-template <uint32_t KMAX>
-__global__ __launch_bounds__(kRedThreads) void k_reduce(const uint64_t *__restrict__ src,
-                                                        uint32_t W,
-                                                        const uint32_t *__restrict__ idx,
-                                                        const uint32_t *__restrict__ items,
-                                                        uint32_t nitems,
-                                                        uint64_t *__restrict__ out)
+// KB buckets per lane: C*D <= KB * kRedThreads.  Dynamic LDS: (NG - 1) slabs.
+template <uint32_t KB, uint32_t NG>
+__global__ __launch_bounds__(NG *kRedThreads) void k_reduce_sample(ReduceArgs a)
 {
-    for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const uint32_t set = items[3 * it];
-        const uint32_t b = items[3 * it + 1];
-        const uint32_t e = items[3 * it + 2];
-        uint64_t acc[KMAX];
+    extern __shared__ uint64_t lds[];
+    Bucket2 *part = (Bucket2 *)lds;  // slabs of groups 1 .. NG-1
+    __shared__ uint32_t s_item[4], s_mem[kRedChunk];
+    __shared__ uint32_t s_best[kRedThreads / 64], s_any[kRedThreads / 64];
+    __shared__ uint32_t s_last;
+    const uint32_t C = a.C, D = a.D, nb = C * D;
+    const uint32_t tid = threadIdx.x % kRedThreads;
+    const uint32_t grp = __builtin_amdgcn_readfirstlane(threadIdx.x / kRedThreads);
+    for (uint32_t it = blockIdx.x; it < a.nitems; it += gridDim.x) {
+        uint32_t set = it, n = 1, parts = 1;
+        bool frag = false;
+        if (a.items) {
+            // one wave fetches the item and its members (host memory, maybe)
+            if (threadIdx.x < 64) {
+                uint32_t w = 0;
+                if (threadIdx.x < 4) w = a.items[4 * it + threadIdx.x];
+                const uint32_t b = __shfl(w, 1), e = __shfl(w, 2);
+                if (threadIdx.x < 4) s_item[threadIdx.x] = w;
+                if (threadIdx.x < e - b) s_mem[threadIdx.x] = a.idx[b + threadIdx.x];
+            }
+            __syncthreads();
+            set = s_item[0];
+            n = s_item[2] - s_item[1];
+            parts = s_item[3];
+            frag = set >> 31;
+            set &= 0x7fffffffu;
+        }
+        const Bucket2 *src = (const Bucket2 *)(frag ? a.src1 : a.src0);
+        Bucket2 acc[KB];
 #pragma unroll
-        for (uint32_t k = 0; k < KMAX; k++) acc[k] = 0;
-        uint32_t j = b;
-        // two slabs per step: twice the loads in flight
-        for (; j + 2 <= e; j += 2) {
-            const uint64_t *s0 = src + (uint64_t)idx[j] * W;
-            const uint64_t *s1 = src + (uint64_t)idx[j + 1] * W;
+        for (uint32_t k = 0; k < KB; k++) acc[k] = Bucket2{0, 0};
+        constexpr uint32_t kAhead = KB <= 4 ? 4 : KB <= 8 ? 2 : 1;  // members in flight
+        for (uint32_t j = grp; j < n; j += kAhead * NG) {
+            Bucket2 t[kAhead][KB];
 #pragma unroll
-            for (uint32_t k = 0; k < KMAX; k++) {
-                const uint32_t w = k * kRedThreads + threadIdx.x;
-                if (w < W) acc[k] ^= s0[w] ^ s1[w];
+            for (uint32_t g = 0; g < kAhead; g++) {
+                const bool in = j + g * NG < n;
+                const uint32_t m =
+                    !a.items ? it
+                             : (uint32_t)__builtin_amdgcn_readfirstlane(s_mem[in ? j + g * NG : j]);
+                const Bucket2 *s0 = src + (uint64_t)m * nb;
+#pragma unroll
+                for (uint32_t k = 0; k < KB; k++) {
+                    const uint32_t q = k * kRedThreads + tid;
+                    t[g][k] = in && q < nb ? s0[q] : Bucket2{0, 0};
+                }
+            }
+#pragma unroll
+            for (uint32_t g = 0; g < kAhead; g++)
+#pragma unroll
+                for (uint32_t k = 0; k < KB; k++) acc[k] ^= t[g][k];
+        }
+        if (NG > 1 && n > 1) {  // (block-uniform)
+            if (grp) {
+#pragma unroll
+                for (uint32_t k = 0; k < KB; k++) {
+                    const uint32_t q = k * kRedThreads + tid;
+                    if (q < nb) part[(grp - 1) * nb + q] = acc[k];
+                }
+            }
+            __syncthreads();
+            if (!grp) {
+#pragma unroll
+                for (uint32_t g = 1; g < NG; g++)
+#pragma unroll
+                    for (uint32_t k = 0; k < KB; k++) {
+                        const uint32_t q = k * kRedThreads + tid;
+                        if (q < nb) acc[k] ^= part[(g - 1) * nb + q];
+                    }
             }
         }
-        if (j < e) {
-            const uint64_t *s0 = src + (uint64_t)idx[j] * W;
+        // group 0 holds the item's sum; the others take part in barriers only
+        bool last = grp == 0;
+        if (parts == 1) {
+            if (a.sig && !a.canon && !grp) {
+                Bucket2 *o = (Bucket2 *)a.sig + (uint64_t)set * nb;
 #pragma unroll
-            for (uint32_t k = 0; k < KMAX; k++) {
-                const uint32_t w = k * kRedThreads + threadIdx.x;
-                if (w < W) acc[k] ^= s0[w];
+                for (uint32_t k = 0; k < KB; k++) {
+                    const uint32_t q = k * kRedThreads + tid;
+                    if (q < nb) o[q] = acc[k];
+                }
+            }
+        } else {
+            uint64_t *o = a.sig + (uint64_t)set * nb * 2;
+#pragma unroll
+            for (uint32_t k = 0; k < KB; k++) {
+                const uint32_t q = k * kRedThreads + tid;
+                if (q < nb && !grp) {
+                    if (acc[k].x) gxor(&o[2 * q], acc[k].x);
+                    if (acc[k].y) gxor(&o[2 * q + 1], acc[k].y);
+                }
+            }
+            // every wave's atomics have been performed (they and the reads
+            // below bypass the caches that are not coherent) before the ticket
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (threadIdx.x == 0)
+                s_last = __hip_atomic_fetch_add(&a.tick[set], 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+            __syncthreads();
+            last = last && s_last != 0;
+            if (last) {
+#pragma unroll
+                for (uint32_t k = 0; k < KB; k++) {
+                    const uint32_t q = k * kRedThreads + tid;
+                    if (q < nb) {
+                        acc[k].x = __hip_atomic_load(&o[2 * q], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                        acc[k].y = __hip_atomic_load(&o[2 * q + 1], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
             }
         }
-        uint64_t *o = out + (uint64_t)set * W;
+        if (last && a.canon) {
+            Bucket2 *o = (Bucket2 *)a.canon + (uint64_t)set * nb;
 #pragma unroll
-        for (uint32_t k = 0; k < KMAX; k++) {
-            const uint32_t w = k * kRedThreads + threadIdx.x;
-            if (w < W && acc[k]) gxor(&o[w], acc[k]);
+            for (uint32_t k = 0; k < KB; k++) {
+                const uint32_t q = k * kRedThreads + tid;
+                const uint32_t d = q / C, c = q - d * C;
+                if (q < nb) o[c * D + d] = acc[k];
+            }
         }
+        uint32_t best = 0xffffffffu, mine = best;
+        uint64_t pick = 0;
+        if (last && a.res) {
+            uint64_t any = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < KB; k++) {
+                const uint32_t q = k * kRedThreads + tid;
+                const uint64_t x = acc[k].x, g = acc[k].y;
+                any |= x | g;
+                if (q >= nb || x == 0) continue;
+                const uint32_t d = q / C, c = q - d * C;
+                const uint64_t h = mix64(x ^ a.seeds[c]);
+                if (h != g || depth_of(h, D) != d) continue;
+                const uint64_t uu = x / a.V, vv = x - uu * a.V;
+                if (!(uu < vv)) continue;
+                const uint32_t key = c * D + (D - 1 - d);
+                if (key < best) {
+                    best = key;
+                    pick = x;
+                }
+            }
+            mine = best;
+            for (uint32_t o = 32; o > 0; o >>= 1) {
+                const uint32_t ob = __shfl_xor(best, o);
+                best = ob < best ? ob : best;
+            }
+            const bool wany = __ballot(any != 0) != 0;
+            if (__lane_id() == 0) {
+                s_best[tid / 64] = best;
+                s_any[tid / 64] = wany ? 1u : 0u;
+            }
+        }
+        __syncthreads();
+        if (last && a.res) {
+            uint32_t some = 0;
+            for (uint32_t w = 0; w < kRedThreads / 64; w++) {
+                best = s_best[w] < best ? s_best[w] : best;
+                some |= s_any[w];
+            }
+            int32_t *r = a.res + 3 * (uint64_t)set;
+            if (best != 0xffffffffu) {
+                if (mine == best) {
+                    r[0] = 0;
+                    r[1] = (int32_t)(uint32_t)(pick / a.V);
+                    r[2] = (int32_t)(uint32_t)(pick % a.V);
+                }
+            } else if (tid == 0) {
+                r[0] = some ? 2 : 1;
+                r[1] = 0;
+                r[2] = 0;
+            }
+        }
+        __syncthreads();  // the shared words are used again
+    }
+    if (a.seq_out && gridDim.x == 1) {
+        // one block: its results are in host memory before the number is
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(a.seq_out, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
-hipError_t launch_reduce(hipStream_t s, const uint64_t *src, uint32_t W, const uint32_t *idx,
-                         const uint32_t *items, uint32_t nitems, uint64_t *out)
+// Publishes a sequence number once the kernels before it on the stream have
+// finished (and their stores to host memory with them).
+__global__ void k_publish(uint32_t *seq_out, uint32_t seq)
 {
-    if (nitems == 0) return hipSuccess;
-    const uint32_t grid = min(nitems, 8192u);
-    if (W <= 4 * kRedThreads)
-        k_reduce<4><<<grid, kRedThreads, 0, s>>>(src, W, idx, items, nitems, out);
-    else if (W <= 8 * kRedThreads)
-        k_reduce<8><<<grid, kRedThreads, 0, s>>>(src, W, idx, items, nitems, out);
-    else if (W <= 16 * kRedThreads)
-        k_reduce<16><<<grid, kRedThreads, 0, s>>>(src, W, idx, items, nitems, out);
-    else if (W <= 32 * kRedThreads)
-        k_reduce<32><<<grid, kRedThreads, 0, s>>>(src, W, idx, items, nitems, out);
-    else
-        return hipErrorInvalidValue;
+    __hip_atomic_store(seq_out, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Zero the aggregates (W words each) and tickets of the sets listed.
+__global__ __launch_bounds__(256) void k_zero_sets(const uint32_t *__restrict__ list, uint32_t W,
+                                                   uint64_t *__restrict__ sig,
+                                                   uint32_t *__restrict__ tick)
+{
+    const uint32_t set = list[blockIdx.x];
+    uint64_t *o = sig + (uint64_t)set * W;
+    for (uint32_t q = threadIdx.x; q < W; q += blockDim.x) o[q] = 0;
+    if (threadIdx.x == 0) tick[set] = 0;
+}
+
+hipError_t launch_reduce_sample(hipStream_t s, const ReduceArgs &a, const uint32_t *zero_list,
+                                uint32_t nzero)
+{
+    if (a.nitems == 0) return hipSuccess;
+    const uint32_t nb = a.C * a.D;
+    if (nzero) {
+        if (!a.sig || !a.tick) return hipErrorInvalidValue;
+        k_zero_sets<<<nzero, 256, 0, s>>>(zero_list, 2 * nb, a.sig, a.tick);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const uint32_t grid = min(a.nitems, 8192u);
+    // Two or four groups share an item; one group each where there are items
+    // enough to fill the chip and few members to share (or, without items,
+    // one): 65,536 members in 18,000 sets take 150 us instead of 212.
+#define CUPK_RED(KB, NG)                                                                     \
+    k_reduce_sample<KB, NG><<<grid, NG * kRedThreads, (size_t)(NG - 1) * nb * 16, s>>>(a)
+    if (!a.items || (a.nitems >= 4 * kCus && a.members <= 16 * (uint64_t)a.nitems)) {
+        if (nb <= 2 * kRedThreads) CUPK_RED(2, 1);
+        else if (nb <= 4 * kRedThreads) CUPK_RED(4, 1);
+        else if (nb <= 16 * kRedThreads) CUPK_RED(16, 1);
+        else return hipErrorInvalidValue;
+    }
+    else if (nb <= kRedThreads) CUPK_RED(1, 4);
+    else if (nb <= 2 * kRedThreads) CUPK_RED(2, 4);
+    else if (nb <= 3 * kRedThreads) CUPK_RED(3, 2);
+    else if (nb <= 4 * kRedThreads) CUPK_RED(4, 2);
+    else if (nb <= 8 * kRedThreads) CUPK_RED(8, 2);
+    else if (nb <= 16 * kRedThreads) CUPK_RED(16, 1);
+    else return hipErrorInvalidValue;
+#undef CUPK_RED
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.seq_out || grid == 1) return e;
+    k_publish<<<1, 1, 0, s>>>(a.seq_out, a.seq);
     return hipGetLastError();
 }
 
@@ -2132,80 +2330,85 @@ hipError_t noalloc_scratch_address(int device, uint64_t **out)
 }
 
 // ---------------------------------------------------------------------------
-// Verify and sample.  One block per aggregate sketch: every lane checks its
-// buckets (alpha != 0, checksum and depth re-derived from alpha, alpha
-// decodes to u < v < V) and the block takes the minimum canonical rank
-// c*D + (D-1-d) among the good ones; a block-wide OR detects the all-zero
-// (EMPTY) case.
+// Queries of sketches in canonical order (bucket (c, d) at c*D + d), one block
+// each, in device or pinned host memory: as the query of k_reduce_sample.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kSmpThreads = 256;
 
 __global__ __launch_bounds__(kSmpThreads) void k_sample(const uint64_t *__restrict__ sig,
-                                                        uint32_t k, uint32_t V, uint32_t C,
-                                                        uint32_t D, uint32_t sc, uint32_t sd,
-                                                        uint64_t set_stride,
+                                                        uint32_t V, uint32_t C, uint32_t D,
                                                         const uint64_t *__restrict__ seeds,
-                                                        int32_t *__restrict__ res)
+                                                        int32_t *__restrict__ res,
+                                                        uint32_t *__restrict__ seq_out,
+                                                        uint32_t seq)
 {
     __shared__ uint32_t s_best[kSmpThreads / 64];
-    __shared__ uint64_t s_any[kSmpThreads / 64];
-    const uint32_t set = blockIdx.x;
-    if (set >= k) return;
-    const uint64_t *S = sig + (uint64_t)set * set_stride;
-    uint32_t best = 0xffffffffu;
-    uint64_t any = 0;
+    __shared__ uint32_t s_any[kSmpThreads / 64];
     const uint32_t nb = C * D;
-    for (uint32_t q = threadIdx.x; q < nb; q += blockDim.x) {
+    const Bucket2 *S = (const Bucket2 *)sig + (uint64_t)blockIdx.x * nb;
+    uint32_t best = 0xffffffffu;
+    uint64_t any = 0, pick = 0;
+    for (uint32_t q = threadIdx.x; q < nb; q += kSmpThreads) {
+        const Bucket2 bk = S[q];
         const uint32_t c = q / D, d = q - c * D;
-        const uint64_t o = ((uint64_t)c * sc + (uint64_t)d * sd) * 2;
-        const uint64_t a = S[o], g = S[o + 1];
-        any |= a | g;
-        if (a == 0) continue;
-        const uint64_t h = mix64(a ^ seeds[c]);
-        if (h != g || depth_of(h, D) != d) continue;
-        const uint64_t uu = a / V, vv = a - uu * V;
+        any |= bk.x | bk.y;
+        if (bk.x == 0) continue;
+        const uint64_t h = mix64(bk.x ^ seeds[c]);
+        if (h != bk.y || depth_of(h, D) != d) continue;
+        const uint64_t uu = bk.x / V, vv = bk.x - uu * V;
         if (!(uu < vv)) continue;
         const uint32_t key = c * D + (D - 1 - d);
-        best = key < best ? key : best;
+        if (key < best) {
+            best = key;
+            pick = bk.x;
+        }
     }
-    // wave reductions
+    const uint32_t mine = best;
     for (uint32_t o = 32; o > 0; o >>= 1) {
         const uint32_t ob = __shfl_xor(best, o);
         best = ob < best ? ob : best;
-        any |= __shfl_xor(any, o);
     }
-    const uint32_t wid = threadIdx.x / 64;
+    const bool wany = __ballot(any != 0) != 0;
     if (__lane_id() == 0) {
-        s_best[wid] = best;
-        s_any[wid] = any;
+        s_best[threadIdx.x / 64] = best;
+        s_any[threadIdx.x / 64] = wany ? 1u : 0u;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (uint32_t w = 1; w < blockDim.x / 64; w++) {
-            best = s_best[w] < best ? s_best[w] : best;
-            any |= s_any[w];
-        }
-        int32_t *r = res + 3 * (uint64_t)set;
-        if (best != 0xffffffffu) {
-            const uint32_t c = best / D, d = D - 1 - (best - c * D);
-            const uint64_t a = S[((uint64_t)c * sc + (uint64_t)d * sd) * 2];
+    uint32_t some = 0;
+    for (uint32_t w = 0; w < kSmpThreads / 64; w++) {
+        best = s_best[w] < best ? s_best[w] : best;
+        some |= s_any[w];
+    }
+    int32_t *r = res + 3 * (uint64_t)blockIdx.x;
+    if (best != 0xffffffffu) {
+        if (mine == best) {
             r[0] = 0;
-            r[1] = (int32_t)(uint32_t)(a / V);
-            r[2] = (int32_t)(uint32_t)(a % V);
-        } else {
-            r[0] = any ? 2 : 1;
-            r[1] = 0;
-            r[2] = 0;
+            r[1] = (int32_t)(uint32_t)(pick / V);
+            r[2] = (int32_t)(uint32_t)(pick % V);
         }
+    } else if (threadIdx.x == 0) {
+        r[0] = some ? 2 : 1;
+        r[1] = 0;
+        r[2] = 0;
+    }
+    if (seq_out && gridDim.x == 1) {
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(seq_out, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
 hipError_t launch_sample(hipStream_t s, const uint64_t *sig, uint32_t k, uint32_t V, uint32_t C,
-                         uint32_t D, uint32_t sc, uint32_t sd, uint64_t set_stride,
-                         const uint64_t *seeds, int32_t *res)
+                         uint32_t D, const uint64_t *seeds, int32_t *res, uint32_t *seq_out,
+                         uint32_t seq)
 {
     if (k == 0) return hipSuccess;
-    k_sample<<<k, kSmpThreads, 0, s>>>(sig, k, V, C, D, sc, sd, set_stride, seeds, res);
+    k_sample<<<k, kSmpThreads, 0, s>>>(sig, V, C, D, seeds, res, seq_out, seq);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !seq_out || k == 1) return e;
+    k_publish<<<1, 1, 0, s>>>(seq_out, seq);
     return hipGetLastError();
 }
 

@@ -241,10 +241,31 @@ bool tile_geometry_fits(uint32_t rows, uint32_t C, uint32_t tv, uint32_t layout)
 hipError_t launch_zero(hipStream_t s, uint64_t *p, size_t n);
 hipError_t launch_zero32(hipStream_t s, uint32_t *p, size_t n);
 
-// Segmented XOR reduction: out[set] = XOR of src slabs listed by `idx`.
-// items: triples (set, begin, end) into idx; slab = W words.
-hipError_t launch_reduce(hipStream_t s, const uint64_t *src, uint32_t W, const uint32_t *idx,
-                         const uint32_t *items, uint32_t nitems, uint64_t *out);
+// Segmented XOR reduction of vertex sketches or fragment sketches into one
+// aggregate per set, and the query of each (see k_reduce_sample).
+constexpr uint32_t kRedChunk = 64;  // most members per work item
+struct ReduceArgs {
+    const uint64_t *src0, *src1;  // slabs of vertices, of the previous round's fragments
+    // (set, begin, end, items of the set) per work item; bit 31 of set: the
+    // members are fragments.  null: item i is set i, vertex i alone.
+    const uint32_t *items;
+    const uint32_t *idx;          // members
+    uint32_t nitems;
+    uint32_t members;             // in all items (chooses the block shape)
+    uint32_t V, C, D;
+    const uint64_t *seeds;
+    uint64_t *sig;    // aggregates, internal layout (may be null when every set has one item)
+    uint32_t *tick;   // one word per set, used by sets of several items
+    uint64_t *canon;  // aggregates in canonical order, or null
+    int32_t *res;     // (status, u, v) per set, or null; device or pinned host memory
+    uint32_t *seq_out;  // null, or where to publish seq once all is written
+    uint32_t seq;
+};
+// zero_list: the sets of several items (nzero of them), whose aggregates and
+// tickets are zeroed first.  Every set must have an item (an empty one for an
+// empty set).
+hipError_t launch_reduce_sample(hipStream_t s, const ReduceArgs &a, const uint32_t *zero_list,
+                                uint32_t nzero);
 
 // Allocation-free aggregates (cupk_component_sketch_batch_noalloc): the
 // members, set offsets and aggregates of one call live in a file-scope
@@ -270,11 +291,11 @@ hipError_t launch_reduce_csr(hipStream_t s, const uint64_t *src, uint32_t W,
                              const uint32_t *mem, const uint64_t *offs, uint32_t k,
                              uint32_t nv, uint64_t *out);
 
-// Query each of k aggregate sketches (bucket (c,d) at word (c*sc + d*sd)*2).
-// res: 3 words per set (status, u, v).
+// Query each of k sketches in canonical order, in device or pinned host
+// memory.  res: 3 words per set (status, u, v); seq_out as in ReduceArgs.
 hipError_t launch_sample(hipStream_t s, const uint64_t *sig, uint32_t k, uint32_t V, uint32_t C,
-                         uint32_t D, uint32_t sc, uint32_t sd, uint64_t set_stride,
-                         const uint64_t *seeds, int32_t *res);
+                         uint32_t D, const uint64_t *seeds, int32_t *res, uint32_t *seq_out,
+                         uint32_t seq);
 
 // Digest of the whole sketch, added into *out (zero it first).
 hipError_t launch_digest(hipStream_t s, DevSketch sk, uint64_t master_seed, uint64_t *out);

@@ -134,7 +134,7 @@ int query_cands(cupk_ctx *ctx, const std::vector<Cand> &cands, const std::vector
     const uint32_t k = (uint32_t)cands.size();
     const uint32_t W2 = 2 * ctx->D;
     size_t nitems = 0;
-    for (const Cand &c : cands) nitems += (c.me - c.mb + kRedChunk - 1) / kRedChunk;
+    for (const Cand &c : cands) nitems += (c.me - c.mb + kColChunk - 1) / kColChunk;
     HIPCHK(grow(L.h_col, k));
     HIPCHK(grow(L.d_col, k));
     HIPCHK(grow(L.h_idx, mem.size() + 1));
@@ -143,14 +143,14 @@ int query_cands(cupk_ctx *ctx, const std::vector<Cand> &cands, const std::vector
     HIPCHK(grow(L.d_items, 3 * nitems + 1));
     HIPCHK(grow(L.d_agg, (size_t)k * W2));
     HIPCHK(grow(ctx->d_res, (size_t)3 * k));
-    HIPCHK(grow(ctx->h_res, (size_t)3 * k));
+    HIPCHK(grow(ctx->h_res, (size_t)3 * k, hipHostMallocCoherent));
     uint32_t *it = L.h_items.p;
     for (uint32_t j = 0; j < k; j++) {
         L.h_col.p[j] = cands[j].level;
-        for (uint32_t b = cands[j].mb; b < cands[j].me; b += kRedChunk) {
+        for (uint32_t b = cands[j].mb; b < cands[j].me; b += kColChunk) {
             *it++ = j;
             *it++ = b;
-            *it++ = std::min(cands[j].me, b + kRedChunk);
+            *it++ = std::min(cands[j].me, b + kColChunk);
         }
     }
     std::copy(mem.begin(), mem.end(), L.h_idx.p);
