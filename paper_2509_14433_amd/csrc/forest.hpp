@@ -335,7 +335,10 @@ class Forest {
     }
     void settle_relabel(const uint32_t *v, size_t n, uint32_t l)
     {
-        for (size_t i = 0; i < n; i++) lbl_[v[i]] = l;
+        for (size_t i = 0; i < n; i++) {
+            lbl_[v[i]] = l;
+            touch(v[i]);
+        }
     }
     // Settle a set of pieces into their final trees in one step (instead of
     // split_pending() and then link_many()).  pieces: (top, group) for every
