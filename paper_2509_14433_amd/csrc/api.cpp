@@ -92,11 +92,15 @@ int harvest_timers(cupk_ctx *ctx, bool all)
     return CUPK_OK;
 }
 
-// Bring the device forest (labels, parents, packed words) up to date on
-// stream st: the pages the host forest wrote since the last upload, through
-// a pinned staging block, when they are fewer than a quarter of all pages;
-// else the whole arrays, copied from the host forest itself (which must then
-// not change until the copy is done).
+// Bring the device forest up to date on stream st, read by the kernel from the
+// host forest's pinned arrays: the pages the host forest wrote since the last
+// upload, or all of it when they are a quarter of all pages or more (through
+// copies beyond kLoadDirect vertices, which the copy engine moves faster).
+// The host forest must then not change until that is done: every caller waits
+// for the header of a pass enqueued behind the upload, or for an event after
+// it, before it touches the forest again.
+constexpr uint32_t kLoadDirect = 1u << 16;
+
 int upload_forest_on(cupk_ctx *ctx, hipStream_t st)
 {
     if (!ctx->forest_dev_stale) return CUPK_OK;
@@ -105,39 +109,25 @@ int upload_forest_on(cupk_ctx *ctx, hipStream_t st)
     pg.clear();
     ctx->forest.take_pages(pg);
     if (pg.empty()) return CUPK_OK;
-    const uint32_t sh = ctx->forest.page_shift(), pv = 1u << sh;
+    const uint32_t sh = ctx->forest.page_shift();
     if (pg.size() * 4 >= ctx->forest.n_pages()) {
-        const size_t bytes = (size_t)ctx->V * sizeof(uint32_t);
-        HIPCHK(hipMemcpyAsync(ctx->d_lbl, ctx->h_lbl, bytes, hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(ctx->d_par, ctx->h_par, bytes, hipMemcpyHostToDevice, st));
-        HIPCHK(launch_pack_forest(st, ctx->d_lbl, ctx->d_par, ctx->d_lp, ctx->V));
-        HIPCHK(launch_block_labels(st, ctx->d_lbl, ctx->V, ctx->d_blk, nullptr, 0, 0));
+        const uint32_t *lbl = ctx->h_lbl, *par = ctx->h_par;
+        if (ctx->V > kLoadDirect) {
+            const size_t bytes = (size_t)ctx->V * sizeof(uint32_t);
+            HIPCHK(hipMemcpyAsync(ctx->d_lbl, lbl, bytes, hipMemcpyHostToDevice, st));
+            HIPCHK(hipMemcpyAsync(ctx->d_par, par, bytes, hipMemcpyHostToDevice, st));
+            lbl = ctx->d_lbl;
+            par = ctx->d_par;
+        }
+        HIPCHK(launch_load_forest(st, lbl, par, ctx->V, nullptr, ((ctx->V - 1) >> sh) + 1, sh,
+                                  ctx->d_lp, ctx->d_blk));
         return CUPK_OK;
     }
-    // the previous staging block has been copied
-    if (ctx->stage_busy) {
-        HIPCHK(hipEventSynchronize(ctx->ev_stage));
-        ctx->stage_busy = false;
-    }
-    const size_t np = pg.size(), words = np * (1 + 2 * (size_t)pv);
-    HIPCHK(grow(ctx->h_stage, words));
-    HIPCHK(grow(ctx->d_stage, words));
-    uint32_t *h = ctx->h_stage.p;
-    std::copy(pg.begin(), pg.end(), h);
-    uint32_t *hl = h + np, *hp = hl + np * pv;
-    for (size_t i = 0; i < np; i++) {
-        const size_t base = (size_t)pg[i] << sh;
-        const size_t m = base < ctx->V ? std::min<size_t>(pv, ctx->V - base) : 0;
-        std::memcpy(hl + i * pv, ctx->h_lbl + base, m * 4);
-        std::memcpy(hp + i * pv, ctx->h_par + base, m * 4);
-    }
-    HIPCHK(hipMemcpyAsync(ctx->d_stage.p, h, words * 4, hipMemcpyHostToDevice, st));
-    HIPCHK(hipEventRecord(ctx->ev_stage, st));
-    ctx->stage_busy = true;
-    HIPCHK(launch_forest_pages(st, ctx->d_stage.p, (uint32_t)np, sh, ctx->V, ctx->d_lbl,
-                               ctx->d_par, ctx->d_lp));
-    HIPCHK(launch_block_labels(st, ctx->d_lbl, ctx->V, ctx->d_blk, ctx->d_stage.p, (uint32_t)np,
-                               sh));
+    // (the previous list has been read: see above)
+    HIPCHK(grow(ctx->h_pages, pg.size(), hipHostMallocCoherent));
+    std::copy(pg.begin(), pg.end(), ctx->h_pages.p);
+    HIPCHK(launch_load_forest(st, ctx->h_lbl, ctx->h_par, ctx->V, ctx->h_pages.p,
+                              (uint32_t)pg.size(), sh, ctx->d_lp, ctx->d_blk));
     return CUPK_OK;
 }
 
@@ -1277,6 +1267,17 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert)
     }
     const bool graph = ctx->opts.use_graph != 0 && !ctx->opts.exact;
     const bool direct = !graph && n > kSmallMax && direct_pays(ctx, n);
+    if (revert && (n <= kSmallMax || direct)) {
+        // the updates have been classified and accepted: only their scatter
+        // (the word tested for a rejected batch is one that stays zero)
+        const uint32_t *zero = &ctx->d_small->hdr[HDR_NFLAG];
+        if (n <= kSmallMax)
+            HIPCHK(launch_small_scatter(ctx->s, d_upd, n, dev_sketch(ctx), zero));
+        else
+            HIPCHK(launch_mid_scatter(ctx->s, d_upd, n, dev_sketch(ctx), zero, nullptr));
+        ctx->ctr.scatter_launches++;
+        return CUPK_OK;
+    }
     // (timed contexts time every pass beyond kSmallMax)
     ctx->small_pass = !graph && (n <= kSmallMax ||
                                  (direct && n <= kOneBlockMax && !ctx->opts.time_kernels));
@@ -1748,8 +1749,7 @@ void destroy(cupk_ctx *ctx)
     release(ctx->h_res);
     release(ctx->h_canon);
     release(ctx->d_tmp);
-    release(ctx->h_stage);
-    release(ctx->d_stage);
+    release(ctx->h_pages);
     for (auto &t : ctx->timers) {
         if (t.t0) (void)hipEventDestroy(t.t0);
         if (t.tb) (void)hipEventDestroy(t.tb);
@@ -1761,7 +1761,6 @@ void destroy(cupk_ctx *ctx)
     if (ctx->ev_scat) (void)hipEventDestroy(ctx->ev_scat);
     if (ctx->ev_up) (void)hipEventDestroy(ctx->ev_up);
     if (ctx->ev_cls) (void)hipEventDestroy(ctx->ev_cls);
-    if (ctx->ev_stage) (void)hipEventDestroy(ctx->ev_stage);
     if (ctx->cs) (void)hipStreamDestroy(ctx->cs);
     if (ctx->own_stream && ctx->s) (void)hipStreamDestroy(ctx->s);
     delete ctx;
@@ -1879,7 +1878,6 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     HIPCHK(hipEventCreateWithFlags(&ctx->ev_scat, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&ctx->ev_up, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&ctx->ev_cls, hipEventDisableTiming));
-    HIPCHK(hipEventCreateWithFlags(&ctx->ev_stage, hipEventDisableTiming));
     if (ctx->opts.time_kernels)
         for (auto &t : ctx->timers) {
             HIPCHK(hipEventCreate(&t.t0));
@@ -1915,6 +1913,7 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     HIPCHK(hipHostMalloc((void **)&ctx->h_desc, sizeof(BatchDesc), hipHostMallocDefault));
     HIPCHK(hipMalloc((void **)&ctx->d_misc, 64));
     HIPCHK(hipMalloc((void **)&ctx->d_small, sizeof(SmallResult)));
+    HIPCHK(hipMemset(ctx->d_small, 0, HDR_WORDS * 4));
     // coherent: the small classify kernel writes its result here directly
     HIPCHK(hipHostMalloc((void **)&ctx->h_small, sizeof(SmallResult), hipHostMallocCoherent));
     memset(ctx->h_small, 0, sizeof(SmallResult));

@@ -518,82 +518,53 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(
 
 uint32_t classify_blocks(uint32_t n) { return (n + kClsPerBlock - 1) / kClsPerBlock; }
 
-__global__ void k_pack_forest(const uint32_t *__restrict__ lbl, const uint32_t *__restrict__ par,
-                              uint64_t *__restrict__ lp, uint32_t V)
+// Refresh of the device forest, one block per page of 2^pshift vertex ids
+// (pages null: page i is block i): packed words lp[w] = label | parent << 32
+// and the label that all 64 ids of a vertex block share, or kBlkMixed.  Bound
+// by latency: lbl and par may be the host forest's own pinned arrays, so that
+// a few pages (or a small forest) take this one launch, which reads them over
+// the host link, instead of copies through a staging block and two or three
+// kernels (a replacement in exact mode took 20 us more).
+__global__ __launch_bounds__(256) void k_load_forest(const uint32_t *__restrict__ lbl,
+                                                     const uint32_t *__restrict__ par, uint32_t V,
+                                                     const uint32_t *__restrict__ pages,
+                                                     uint32_t pshift, uint64_t *__restrict__ lp,
+                                                     uint32_t *__restrict__ blk)
 {
-    for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < V; w += gridDim.x * blockDim.x)
-        lp[w] = (uint64_t)lbl[w] | (uint64_t)par[w] << 32;
-}
-
-// One wave per block of 2^kBlkShift = 64 vertex ids: the label they all
-// share, or kBlkMixed.  pages null: every block; else the blocks of the np
-// pages (2^pshift ids each) listed there.
-__global__ void k_block_labels(const uint32_t *__restrict__ lbl, uint32_t V,
-                               uint32_t *__restrict__ blk, const uint32_t *__restrict__ pages,
-                               uint32_t np, uint32_t pshift)
-{
-    const uint32_t nblk = (V + 63) >> kBlkShift;
-    const uint32_t per = pages ? 1u << (pshift - kBlkShift) : 0u;  // blocks per page
-    const uint32_t nw = pages ? np * per : nblk;
+    const uint32_t base = (pages ? pages[blockIdx.x] : blockIdx.x) << pshift;
     const uint32_t lane = __lane_id();
-    for (uint32_t w = (blockIdx.x * blockDim.x + threadIdx.x) / 64; w < nw;
-         w += gridDim.x * blockDim.x / 64) {
-        const uint32_t b = pages ? (pages[w / per] << (pshift - kBlkShift)) + w % per : w;
-        if (b >= nblk) continue;  // (wave-uniform) past the last vertex
-        const uint32_t x = (b << kBlkShift) + lane;
-        const uint32_t l = x < V ? lbl[x] : 0u;
-        const uint32_t first = __shfl(l, 0);
-        const uint64_t differ = __ballot(x < V && l != first);
-        if (lane == 0) blk[b] = differ ? kBlkMixed : first;
+    constexpr uint32_t kAhead = 4;  // vertex blocks of a wave in flight
+    for (uint32_t i0 = threadIdx.x / 64; i0 < 1u << (pshift - kBlkShift); i0 += 4 * kAhead) {
+        uint32_t l[kAhead], q[kAhead];
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; k++) {
+            const uint32_t i = i0 + 4 * k, w = base + (i << kBlkShift) + lane;
+            l[k] = q[k] = 0;
+            if (i < 1u << (pshift - kBlkShift) && w < V) {
+                l[k] = lbl[w];
+                q[k] = par[w];
+            }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; k++) {
+            const uint32_t i = i0 + 4 * k, w = base + (i << kBlkShift) + lane;
+            const bool in = i < 1u << (pshift - kBlkShift) && w < V;
+            if (in) lp[w] = (uint64_t)l[k] | (uint64_t)q[k] << 32;
+            const uint32_t first = __shfl(l[k], 0);
+            const uint64_t differ = __ballot(in && l[k] != first);
+            if (in && lane == 0) blk[w >> kBlkShift] = differ ? kBlkMixed : first;
+        }
     }
 }
 
-hipError_t launch_block_labels(hipStream_t s, const uint32_t *lbl, uint32_t V, uint32_t *blk,
-                               const uint32_t *pages, uint32_t np, uint32_t pshift)
+hipError_t launch_load_forest(hipStream_t s, const uint32_t *lbl, const uint32_t *par, uint32_t V,
+                              const uint32_t *pages, uint32_t np, uint32_t pshift, uint64_t *lp,
+                              uint32_t *blk)
 {
-    if (V == 0 || (pages && np == 0)) return hipSuccess;
-    if (pages && (pshift < kBlkShift || pshift > 16)) return hipErrorInvalidValue;
-    const uint32_t nw = pages ? np << (pshift - kBlkShift) : (V + 63) >> kBlkShift;
-    const uint32_t grid = min((nw + 3) / 4, 8192u);
-    k_block_labels<<<grid, 256, 0, s>>>(lbl, V, blk, pages, np, pshift);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_forest(hipStream_t s, const uint32_t *lbl, const uint32_t *par, uint64_t *lp,
-                              uint32_t V)
-{
-    if (V == 0) return hipSuccess;
-    const uint32_t grid = min((V + 255) / 256, 8192u);
-    k_pack_forest<<<grid, 256, 0, s>>>(lbl, par, lp, V);
-    return hipGetLastError();
-}
-
-// Page i of the staging block (id stage[i], then 2^pshift labels of each
-// page in turn, then 2^pshift parents of each page in turn) into lbl, par
-// and lp.
-__global__ void k_forest_pages(const uint32_t *__restrict__ stage, uint32_t np, uint32_t pshift,
-                               uint32_t V, uint32_t *__restrict__ lbl, uint32_t *__restrict__ par,
-                               uint64_t *__restrict__ lp)
-{
-    const uint32_t i = blockIdx.x;
-    const uint32_t pv = 1u << pshift;
-    const uint32_t base = stage[i] << pshift;
-    const uint32_t *sl = stage + np + (size_t)i * pv;
-    const uint32_t *sp = stage + np + (size_t)np * pv + (size_t)i * pv;
-    for (uint32_t j = threadIdx.x; j < pv && base + j < V; j += blockDim.x) {
-        const uint32_t w = base + j, l = sl[j], q = sp[j];
-        lbl[w] = l;
-        par[w] = q;
-        lp[w] = (uint64_t)l | (uint64_t)q << 32;
-    }
-}
-
-hipError_t launch_forest_pages(hipStream_t s, const uint32_t *stage, uint32_t np, uint32_t pshift,
-                               uint32_t V, uint32_t *lbl, uint32_t *par, uint64_t *lp)
-{
-    if (np == 0) return hipSuccess;
-    if (pshift > 16 || ((size_t)(V - 1) >> pshift) >= (1u << 31)) return hipErrorInvalidValue;
-    k_forest_pages<<<np, 256, 0, s>>>(stage, np, pshift, V, lbl, par, lp);
+    if (np == 0 || V == 0) return hipSuccess;
+    if (pshift < kBlkShift || pshift > 16 || ((size_t)(V - 1) >> pshift) >= (1u << 31))
+        return hipErrorInvalidValue;
+    k_load_forest<<<np, 256, 0, s>>>(lbl, par, V, pages, pshift, lp, blk);
     return hipGetLastError();
 }
 
@@ -913,6 +884,9 @@ hipError_t launch_small_classify(hipStream_t s, const uint64_t *upd, uint32_t n,
     const uint32_t wp = with_pos ? 1u : 0u;
     if (n <= kSmallMax)
         k_small_classify<kSmallMax / kSmallThreads>
+            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, out, derr, seqp, wp);
+    else if (n <= kOneBlockMax / 2)
+        k_small_classify<kOneBlockMax / 2 / kSmallThreads>
             <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, out, derr, seqp, wp);
     else
         k_small_classify<kOneBlockMax / kSmallThreads>

@@ -123,8 +123,8 @@ struct StagedParams {
 // stores at tile_rel[b*ntiles + t] where its records start among the
 // records of count copy b % kCntGroups in tile t (written only for tiles it
 // has records in), so that the fill reserves nothing.
-// blk (may be null): the block labels (launch_block_labels) of the forest
-// in lp; inserts between two uniform blocks then skip the forest words.
+// blk (may be null): the block labels (launch_load_forest) of the forest in
+// lp; inserts between two uniform blocks then skip the forest words.
 constexpr uint32_t kRelMaxTiles = 2048;
 hipError_t launch_classify(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32_t grid_n,
                            uint32_t V, const uint64_t *lp, const uint32_t *blk, uint32_t *hdr,
@@ -132,24 +132,19 @@ hipError_t launch_classify(hipStream_t s, const BatchDesc *desc, BatchDesc dv, u
                            uint32_t tile_shift, uint32_t ntiles, const ScanArgs &sa,
                            uint32_t *hout, const FlagInline &fi, uint32_t *tile_rel);
 uint32_t classify_blocks(uint32_t n);
-// lp[w] = lbl[w] | par[w] << 32 (the forest as the classify kernel reads it:
-// one 8-byte load per endpoint gives its label and its parent).
-hipError_t launch_pack_forest(hipStream_t s, const uint32_t *lbl, const uint32_t *par, uint64_t *lp,
-                              uint32_t V);
-// Block labels: blk[b] (b < ceil(V / 64)) = the label that all vertex ids
-// [64 b, 64 b + 64) below V share, or kBlkMixed.  With `pages` (np page ids
-// in device memory, pages of 2^pshift ids, pshift in [6, 16]) only the
-// blocks of those pages are recomputed.  The classify kernel (blk non-null)
-// decides an insert whose endpoints both lie in uniform blocks by them.
+// The device forest as the classify kernels read it: lp[w] = label | parent
+// << 32 (one 8-byte load per endpoint) and the block labels blk[b] (b <
+// ceil(V / 64)): the label that all vertex ids [64 b, 64 b + 64) below V
+// share, or kBlkMixed; the classify kernel (blk non-null) decides an insert
+// whose endpoints both lie in uniform blocks by them.  Refreshes np pages of
+// 2^pshift ids (pshift in [6, 16]): those listed in `pages`, or, when it is
+// null, pages 0 .. np-1.  lbl, par (indexed by vertex) and pages: device or
+// pinned host memory.
 constexpr uint32_t kBlkShift = 6;
 constexpr uint32_t kBlkMixed = 0xffffffffu;
-hipError_t launch_block_labels(hipStream_t s, const uint32_t *lbl, uint32_t V, uint32_t *blk,
-                               const uint32_t *pages, uint32_t np, uint32_t pshift);
-// Refresh np pages of 2^pshift vertices of the device forest from a staging
-// block: np page ids, then each page's labels in turn, then each page's
-// parents in turn (2^pshift words per page; entries past V are ignored).
-hipError_t launch_forest_pages(hipStream_t s, const uint32_t *stage, uint32_t np, uint32_t pshift,
-                               uint32_t V, uint32_t *lbl, uint32_t *par, uint64_t *lp);
+hipError_t launch_load_forest(hipStream_t s, const uint32_t *lbl, const uint32_t *par, uint32_t V,
+                              const uint32_t *pages, uint32_t np, uint32_t pshift, uint64_t *lp,
+                              uint32_t *blk);
 // Second half of a classification launched with fi.tiles_only = 1: with
 // `check`, keep, in each classify block's region of fi.fupd (in place,
 // stream order kept), only the updates the classify kernel's rule flags
