@@ -149,7 +149,7 @@ struct RoundSet {
 // on.  every: milliseconds between queries (0: every 256 spins); a query of a
 // busy stream can queue a marker, which idles the GPU for a few microseconds
 // between two kernels.
-static int wait_word(cupk_ctx *ctx, const uint32_t *w, uint32_t seq, hipStream_t st, double every)
+int wait_word(cupk_ctx *ctx, const uint32_t *w, uint32_t seq, hipStream_t st, double every)
 {
     double next_query = 0;
     for (uint32_t spin = 1;; spin++) {
@@ -173,11 +173,6 @@ static int wait_word(cupk_ctx *ctx, const uint32_t *w, uint32_t seq, hipStream_t
     }
 }
 
-// Members and work items up to this many words are read by the kernel from
-// pinned host memory, and the results of up to kDirectSets sets written
-// there; beyond, copies are faster.
-constexpr size_t kDirectWords = 1u << 16;
-constexpr uint32_t kDirectSets = 4096;
 // Sketches up to this many bytes pass between host arrays and kernels through
 // a pinned block that the kernel reads or writes itself.
 constexpr size_t kDirectBytes = (size_t)256 << 10;

@@ -22,7 +22,11 @@
 
 namespace cupk {
 
-constexpr uint32_t kColChunk = 16;          // members per one-column reduction work item
+// Members and work items up to this many words are read by the kernels from
+// pinned host memory, and the results of up to kDirectSets sets written
+// there; beyond, copies are faster.
+constexpr size_t kDirectWords = 1u << 16;
+constexpr uint32_t kDirectSets = 4096;
 constexpr size_t kMaxBatchPerLaunch = 1u << 28;
 constexpr int kTimerRing = 64;
 
@@ -272,6 +276,7 @@ int upload_forest(cupk_ctx *ctx);
 int reduce_and_sample(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vmem,
                       const std::vector<uint32_t> &voff, const std::vector<uint32_t> &fmem,
                       const std::vector<uint32_t> &foff);
+int wait_word(cupk_ctx *ctx, const uint32_t *w, uint32_t seq, hipStream_t st, double every);
 int run_rounds(cupk_ctx *ctx);
 int flush_pending(cupk_ctx *ctx);
 

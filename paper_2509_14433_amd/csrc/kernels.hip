@@ -2387,97 +2387,97 @@ hipError_t launch_sample(hipStream_t s, const uint64_t *sig, uint32_t k, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// One-column aggregates for the multi-level hierarchy: set k is reduced over
-// column col[k] only (level col[k]'s sampler).  A wave takes one work item
-// (set, members [b, e)) at a time; lane l < 2D holds word l of the
-// aggregate (depth l/2, alpha or gamma), read from each member's slab with a
-// stride of one bucket row; the result is XORed into out[k*2D + l].
+// One-column aggregates for the multi-level hierarchy, each queried in the
+// same launch: as k_reduce_sample, but a wave takes a work item and lane d
+// holds depth d's bucket of the set's column, so that a set of one item never
+// leaves registers.  The deepest good bucket wins (depths are scanned from D-1
+// down).  Bound by latency and by the lines of the members' buckets, one per
+// depth; several members' loads are in flight.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kColThreads = 256;
 
-__global__ __launch_bounds__(kColThreads) void k_reduce_col(
-    const uint64_t *__restrict__ sk, uint32_t C, uint32_t D, const uint32_t *__restrict__ idx,
-    const uint32_t *__restrict__ items, uint32_t nitems, const uint32_t *__restrict__ col,
-    uint64_t *__restrict__ out)
+__global__ __launch_bounds__(kColThreads) void k_reduce_sample_col(ReduceArgs a)
 {
+    const uint32_t C = a.C, D = a.D;
     const uint32_t lane = __lane_id();
-    const uint32_t waves = kColThreads / 64;
-    const uint32_t W2 = 2 * D;
-    for (uint32_t it = blockIdx.x * waves + threadIdx.x / 64; it < nitems;
-         it += gridDim.x * waves) {
-        const uint32_t set = items[3 * it], b = items[3 * it + 1], e = items[3 * it + 2];
-        const uint32_t c = col[set];
-        for (uint32_t l = lane; l < W2; l += 64) {
-            const uint32_t d = l >> 1;
-            uint64_t acc = 0;
-            for (uint32_t m = b; m < e; m++) {
-                const uint64_t w = idx[m];
-                acc ^= sk[((w * D + d) * C + c) * 2 + (l & 1)];
+    const uint32_t wave = blockIdx.x * (kColThreads / 64) + threadIdx.x / 64;
+    const uint32_t nwaves = gridDim.x * (kColThreads / 64);
+    for (uint32_t it = wave; it < a.nitems; it += nwaves) {
+        const uint32_t w = lane < 4 ? a.items[4 * it + lane] : 0u;
+        const uint32_t set = __builtin_amdgcn_readlane(w, 0);
+        const uint32_t b = __builtin_amdgcn_readlane(w, 1), e = __builtin_amdgcn_readlane(w, 2);
+        const uint32_t pc = __builtin_amdgcn_readlane(w, 3);
+        const uint32_t parts = pc & 0xffffffu, c = pc >> 24;
+        const uint32_t mem = lane < e - b ? a.idx[b + lane] : 0u;
+        const Bucket2 *sk = (const Bucket2 *)a.src0 + (uint64_t)(lane < D ? lane : 0) * C + c;
+        Bucket2 acc{0, 0};
+        constexpr uint32_t kAhead = 8;
+        for (uint32_t j = 0; j < e - b; j += kAhead) {
+            Bucket2 t[kAhead];
+#pragma unroll
+            for (uint32_t g = 0; g < kAhead; g++) {
+                const bool in = j + g < e - b;
+                const uint64_t m = (uint32_t)__builtin_amdgcn_readlane(mem, in ? j + g : 0);
+                t[g] = in && lane < D ? sk[m * D * C] : Bucket2{0, 0};
             }
-            if (acc) gxor(out + (uint64_t)set * W2 + l, acc);
+#pragma unroll
+            for (uint32_t g = 0; g < kAhead; g++) acc ^= t[g];
+        }
+        if (parts > 1) {  // (wave-uniform)
+            uint64_t *o = a.sig + ((uint64_t)set * D + lane) * 2;
+            if (lane < D) {
+                if (acc.x) gxor(o, acc.x);
+                if (acc.y) gxor(o + 1, acc.y);
+            }
+            // the wave's atomics have been performed before its ticket
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            uint32_t t = 0;
+            if (lane == 0)
+                t = __hip_atomic_fetch_add(&a.tick[set], 1u, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_readlane(t, 0) != parts - 1) continue;
+            if (lane < D) {
+                acc.x = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                acc.y = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        bool good = false;
+        if (lane < D && acc.x != 0) {
+            const uint64_t h = mix64(acc.x ^ a.seeds[c]);
+            const uint64_t uu = acc.x / a.V, vv = acc.x - uu * a.V;
+            good = h == acc.y && depth_of(h, D) == lane && uu < vv;
+        }
+        const uint64_t mg = __ballot(good);
+        const uint64_t mz = __ballot(lane < D && (acc.x | acc.y) != 0);
+        const uint32_t top = mg ? 63u - (uint32_t)__builtin_clzll(mg) : 0u;
+        if (lane == top) {
+            int32_t *r = a.res + 3 * (uint64_t)set;
+            r[0] = mg ? 0 : mz ? 2 : 1;
+            r[1] = mg ? (int32_t)(uint32_t)(acc.x / a.V) : 0;
+            r[2] = mg ? (int32_t)(uint32_t)(acc.x % a.V) : 0;
         }
     }
 }
 
-hipError_t launch_reduce_col(hipStream_t s, const uint64_t *sk, uint32_t C, uint32_t D,
-                             const uint32_t *idx, const uint32_t *items, uint32_t nitems,
-                             const uint32_t *col, uint64_t *out)
+hipError_t launch_reduce_sample_col(hipStream_t s, const ReduceArgs &a, const uint32_t *zero_list,
+                                    uint32_t nzero)
 {
-    if (nitems == 0) return hipSuccess;
+    if (a.nitems == 0) return hipSuccess;
+    if (a.D > 64 || !a.items || !a.res) return hipErrorInvalidValue;
+    if (nzero) {
+        if (!a.sig || !a.tick) return hipErrorInvalidValue;
+        k_zero_sets<<<nzero, 64, 0, s>>>(zero_list, 2 * a.D, a.sig, a.tick);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     const uint32_t waves = kColThreads / 64;
-    const uint32_t grid = min((nitems + waves - 1) / waves, 8192u);
-    k_reduce_col<<<grid, kColThreads, 0, s>>>(sk, C, D, idx, items, nitems, col, out);
-    return hipGetLastError();
-}
-
-// Query of one column: a wave per set; lane d checks bucket d of the
-// set's one-column aggregate; the deepest good bucket wins (depths are
-// scanned from D-1 down).
-__global__ __launch_bounds__(kColThreads) void k_sample_col(
-    const uint64_t *__restrict__ agg, uint32_t k, uint32_t V, uint32_t D,
-    const uint32_t *__restrict__ col, const uint64_t *__restrict__ seeds, int32_t *__restrict__ res)
-{
-    const uint32_t lane = __lane_id();
-    const uint32_t set = blockIdx.x * (kColThreads / 64) + threadIdx.x / 64;
-    if (set >= k) return;
-    const uint64_t *A = agg + (uint64_t)set * 2 * D;
-    const uint64_t seed = seeds[col[set]];
-    uint64_t a = 0, g = 0;
-    bool good = false;
-    if (lane < D) {
-        a = A[2 * lane];
-        g = A[2 * lane + 1];
-        if (a != 0) {
-            const uint64_t h = mix64(a ^ seed);
-            const uint64_t uu = a / V, vv = a - uu * V;
-            good = h == g && depth_of(h, D) == lane && uu < vv;
-        }
-    }
-    const uint64_t mg = __ballot(good);
-    const uint64_t mz = __ballot((a | g) != 0);
-    const uint32_t top = mg ? 63u - (uint32_t)__builtin_clzll(mg) : 0u;
-    const uint64_t pick = __shfl(a, (int)top);
-    if (lane == 0) {
-        int32_t *r = res + 3 * (uint64_t)set;
-        if (mg) {
-            r[0] = 0;
-            r[1] = (int32_t)(uint32_t)(pick / V);
-            r[2] = (int32_t)(uint32_t)(pick % V);
-        } else {
-            r[0] = mz ? 2 : 1;
-            r[1] = 0;
-            r[2] = 0;
-        }
-    }
-}
-
-hipError_t launch_sample_col(hipStream_t s, const uint64_t *agg, uint32_t k, uint32_t V,
-                             uint32_t D, const uint32_t *col, const uint64_t *seeds,
-                             int32_t *res)
-{
-    if (k == 0) return hipSuccess;
-    const uint32_t waves = kColThreads / 64;
-    k_sample_col<<<(k + waves - 1) / waves, kColThreads, 0, s>>>(agg, k, V, D, col, seeds, res);
+    const uint32_t grid = min((a.nitems + waves - 1) / waves, 8192u);
+    k_reduce_sample_col<<<grid, kColThreads, 0, s>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.seq_out) return e;
+    k_publish<<<1, 1, 0, s>>>(a.seq_out, a.seq);
     return hipGetLastError();
 }
 

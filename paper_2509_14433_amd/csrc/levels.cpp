@@ -126,47 +126,77 @@ void gather(cupk_ctx *ctx, uint32_t lo, std::vector<Cand> &cands, std::vector<ui
     }
 }
 
-// One launch pair over all candidates: one-column reduction of each
-// candidate's members, then its level's query; results in ctx->h_res.
+// One launch over all candidates: one-column reduction of each candidate's
+// members and its level's query; results in ctx->h_res.
 int query_cands(cupk_ctx *ctx, const std::vector<Cand> &cands, const std::vector<uint32_t> &mem)
 {
     Levels &L = *ctx->levels;
     const uint32_t k = (uint32_t)cands.size();
-    const uint32_t W2 = 2 * ctx->D;
-    size_t nitems = 0;
-    for (const Cand &c : cands) nitems += (c.me - c.mb + kColChunk - 1) / kColChunk;
-    HIPCHK(grow(L.h_col, k));
-    HIPCHK(grow(L.d_col, k));
-    HIPCHK(grow(L.h_idx, mem.size() + 1));
-    HIPCHK(grow(L.d_idx, mem.size() + 1));
-    HIPCHK(grow(L.h_items, 3 * nitems + 1));
-    HIPCHK(grow(L.d_items, 3 * nitems + 1));
-    HIPCHK(grow(L.d_agg, (size_t)k * W2));
-    HIPCHK(grow(ctx->d_res, (size_t)3 * k));
+    auto parts_of = [](const Cand &c) {
+        const uint32_t n = c.me - c.mb;
+        return n <= kRedChunk ? 1u : (n + kRedChunk - 1) / kRedChunk;
+    };
+    size_t nitems = 0, nzero = 0;
+    for (const Cand &c : cands) {
+        const uint32_t p = parts_of(c);
+        nitems += p;
+        nzero += p > 1;
+    }
+    // members, items and the sets to zero, in one buffer
+    const size_t nall = mem.size() + 4 * nitems + nzero;
+    const bool direct = nall <= kDirectWords, pub = k <= kDirectSets;
+    HIPCHK(grow(L.h_idx, nall + 1, hipHostMallocCoherent));
+    if (!direct) HIPCHK(grow(L.d_idx, nall + 1));
+    if (nzero) {
+        HIPCHK(grow(L.d_agg, (size_t)k * 2 * ctx->D));
+        HIPCHK(grow(ctx->d_tick, k));
+    }
     HIPCHK(grow(ctx->h_res, (size_t)3 * k, hipHostMallocCoherent));
-    uint32_t *it = L.h_items.p;
+    if (!pub) HIPCHK(grow(ctx->d_res, (size_t)3 * k));
+    uint32_t *it = L.h_idx.p + mem.size(), *zl = it + 4 * nitems;
+    std::copy(mem.begin(), mem.end(), L.h_idx.p);
     for (uint32_t j = 0; j < k; j++) {
-        L.h_col.p[j] = cands[j].level;
-        for (uint32_t b = cands[j].mb; b < cands[j].me; b += kColChunk) {
-            *it++ = j;
-            *it++ = b;
-            *it++ = std::min(cands[j].me, b + kColChunk);
+        const Cand &c = cands[j];
+        const uint32_t p = parts_of(c);
+        if (p > 1) *zl++ = j;
+        for (uint32_t q = 0; q < p; q++, it += 4) {
+            it[0] = j;
+            it[1] = c.mb + q * kRedChunk;
+            it[2] = std::min(c.me, c.mb + (q + 1) * kRedChunk);
+            it[3] = p | c.level << 24;
         }
     }
-    std::copy(mem.begin(), mem.end(), L.h_idx.p);
     hipStream_t s = ctx->s;
-    HIPCHK(hipMemcpyAsync(L.d_col.p, L.h_col.p, (size_t)k * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(L.d_idx.p, L.h_idx.p, mem.size() * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(L.d_items.p, L.h_items.p, 3 * nitems * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(launch_zero(s, L.d_agg.p, (size_t)k * W2));
-    HIPCHK(launch_reduce_col(s, ctx->d_sk, ctx->C, ctx->D, L.d_idx.p, L.d_items.p,
-                             (uint32_t)nitems, L.d_col.p, L.d_agg.p));
-    HIPCHK(launch_sample_col(s, L.d_agg.p, k, ctx->V, ctx->D, L.d_col.p, ctx->d_seeds,
-                             ctx->d_res.p));
-    HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, (size_t)3 * k * 4, hipMemcpyDeviceToHost,
-                          s));
-    // the pinned staging above is written again by the next pass
-    HIPCHK(hipStreamSynchronize(s));
+    const uint32_t *base = L.h_idx.p;
+    if (!direct) {
+        HIPCHK(hipMemcpyAsync(L.d_idx.p, base, nall * 4, hipMemcpyHostToDevice, s));
+        base = L.d_idx.p;
+    }
+    ReduceArgs a = {};
+    a.src0 = ctx->d_sk;
+    a.items = base + mem.size();
+    a.idx = base;
+    a.nitems = (uint32_t)nitems;
+    a.V = ctx->V;
+    a.C = ctx->C;
+    a.D = ctx->D;
+    a.seeds = ctx->d_seeds;
+    a.sig = L.d_agg.p;
+    a.tick = ctx->d_tick.p;
+    a.res = pub ? ctx->h_res.p : ctx->d_res.p;
+    if (pub) {
+        a.seq_out = ctx->h_pub;
+        a.seq = ++ctx->pub_seq;
+    }
+    HIPCHK(launch_reduce_sample_col(s, a, base + mem.size() + 4 * nitems, (uint32_t)nzero));
+    if (pub) {
+        const int rc = wait_word(ctx, ctx->h_pub, a.seq, s, 1.0);
+        if (rc != CUPK_OK) return rc;
+    } else {
+        HIPCHK(hipMemcpyAsync(ctx->h_res.p, ctx->d_res.p, (size_t)3 * k * 4,
+                              hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+    }
     ctx->ctr.sets_reduced += k;
     ctx->ctr.slabs_reduced += mem.size();
     return CUPK_OK;
@@ -195,12 +225,8 @@ void levels_release(cupk_ctx *ctx)
 {
     if (!ctx->levels) return;
     Levels &L = *ctx->levels;
-    release(L.d_col);
     release(L.d_idx);
-    release(L.d_items);
-    release(L.h_col);
     release(L.h_idx);
-    release(L.h_items);
     release(L.d_agg);
 }
 

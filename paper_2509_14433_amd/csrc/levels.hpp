@@ -12,7 +12,7 @@
 // (in stream order) leave every level from the edge's weight up; then
 // restore() re-establishes Invariant 3 (a level-i component whose query
 // succeeds is a proper subset of its level-(i+1) component) in passes, each
-// one GPU launch pair (one-column reduce + query) over every component that
+// one GPU launch (one-column reduce + query) over every component that
 // could violate it, repairs at the lowest violating level as in Alg. 1
 // (cycle edge = heaviest edge of the top-forest path, removed from its
 // weight up; the sampled edge joins every level above), and finally
@@ -32,8 +32,8 @@ struct Level {
 struct Levels {
     uint32_t top = 0;                       // = C
     std::vector<std::unique_ptr<Level>> lv; // lv[j] for j = 1..top-1 (lv[0] empty)
-    DevBuf<uint32_t> d_col, d_idx, d_items;
-    HostBuf<uint32_t> h_col, h_idx, h_items;
+    DevBuf<uint32_t> d_idx;
+    HostBuf<uint32_t> h_idx;
     DevBuf<uint64_t> d_agg;
     std::vector<uint32_t> mark;             // scratch of path searches
     uint32_t epoch = 0;
