@@ -894,6 +894,31 @@ bool apply_flags(cupk_ctx *ctx, const uint64_t *upd, uint32_t k0, uint32_t k1, b
     return done || (all_inserts && F.n_trees() == 1);
 }
 
+// Coarse bins of the two-level binning: records per work item of the second
+// fill, and the most items of a batch of n updates.
+static uint32_t coarse_chunk(const cupk_ctx *ctx)
+{
+    return fine_chunk(rec_wide(ctx->V, ctx->tile_shift + ctx->fshift));
+}
+static uint32_t coarse_items(const cupk_ctx *ctx, size_t n)
+{
+    return (uint32_t)(2 * n / coarse_chunk(ctx)) + ctx->ncoarse;
+}
+
+// The staged scatter's records and work items for batches of up to cap
+// updates and the geometry in force.
+static int ensure_bins(cupk_ctx *ctx, size_t cap)
+{
+    HIPCHK(grow(ctx->d_bins, 2 * cap * (rec_wide(ctx->V, ctx->tile_shift) ? 2 : 1)));
+    if (ctx->fshift) {
+        const bool wide = rec_wide(ctx->V, ctx->tile_shift + ctx->fshift);
+        HIPCHK(grow(ctx->d_bins1, 2 * cap * (wide ? 2 : 1)));
+        HIPCHK(grow(ctx->d_citems, 2 + 2 * (size_t)coarse_items(ctx, cap)));
+    }
+    HIPCHK(grow(ctx->d_items, 2 * (2 * cap / ctx->chunk + ctx->ntiles + 1)));
+    return CUPK_OK;
+}
+
 // Size every per-batch buffer for one capacity (updates per batch); growth
 // is geometric.  Captured graphs embed buffer pointers and are dropped.
 int ensure_batch_buffers(cupk_ctx *ctx, size_t n)
@@ -914,10 +939,8 @@ int ensure_batch_buffers(cupk_ctx *ctx, size_t n)
         HIPCHK(grow(ctx->h_fpos, cap));
     }
     if (ctx->opts.scatter_mode == CUPK_SCATTER_STAGED) {
-        HIPCHK(grow(ctx->d_bins, 2 * cap));
-        if (ctx->fshift) HIPCHK(grow(ctx->d_bins1, 2 * cap));
-        const size_t icap = 2 * cap / ctx->chunk + ctx->ntiles + 1;
-        HIPCHK(grow(ctx->d_items, 2 * icap));
+        int rc = ensure_bins(ctx, cap);
+        if (rc != CUPK_OK) return rc;
     }
     ctx->batch_cap = cap;
     return ensure_rel(ctx);
@@ -1033,14 +1056,15 @@ int enqueue_classify(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n, bool tiles_o
     uint32_t cls_shift = ctx->tile_shift, cls_tiles = ctx->ntiles;
     if (staged && ctx->fshift) {
         // two-level: the classify kernel and its scan work on coarse bins
-        // (the tile counts come later, from the coarse-binned records)
+        // (the tile counts come later, from the coarse-binned records); the
+        // work items are the second fill's
         sa = {};
         sa.off = ctx->d_coff.p;
         sa.cur = ctx->d_ccur.p;
-        sa.items = ctx->d_csink.p;
-        sa.nitems = ctx->d_csink.p + 2;
-        sa.chunk = 1u << 30;
-        sa.items_cap = 0;
+        sa.items = ctx->d_citems.p + 2;
+        sa.nitems = ctx->d_citems.p;
+        sa.chunk = coarse_chunk(ctx);
+        sa.items_cap = coarse_items(ctx, grid_n);
         sa.groups = 1;
         cnt = ctx->d_ccnt.p;
         cls_shift = ctx->tile_shift + ctx->fshift;
@@ -1083,9 +1107,9 @@ int enqueue_bin(cupk_ctx *ctx, hipStream_t s, uint32_t grid_n)
     sa.items_cap = p.items_cap;
     sa.groups = 1;
     sa.sums = ctx->d_tsum.p;
-    HIPCHK(launch_fine(s, grid_n, ctx->d_hdr, ctx->d_bins1.p, ctx->d_coff.p + ctx->ncoarse,
-                       ctx->tile_shift, ctx->fshift, ctx->ntiles, ctx->d_tcnt.p, sa,
-                       ctx->d_bins.p));
+    HIPCHK(launch_fine(s, grid_n, ctx->V, ctx->d_hdr, ctx->d_bins1.p, ctx->d_coff.p,
+                       ctx->d_citems.p + 2, ctx->d_citems.p, ctx->tile_shift, ctx->fshift,
+                       ctx->ntiles, ctx->d_tcnt.p, sa, ctx->d_bins.p));
     return CUPK_OK;
 }
 
@@ -1734,7 +1758,7 @@ void destroy(cupk_ctx *ctx)
     release(ctx->d_cgoff);
     release(ctx->d_coff);
     release(ctx->d_ccur);
-    release(ctx->d_csink);
+    release(ctx->d_citems);
     release(ctx->d_ridx);
     release(ctx->h_ridx);
     release(ctx->d_sig[0]);
@@ -1817,9 +1841,7 @@ int set_geometry(cupk_ctx *ctx, uint32_t tv, uint32_t rows, uint32_t chunk, uint
         HIPCHK(grow(ctx->d_cgoff, nc));
         HIPCHK(grow(ctx->d_coff, ctx->ncoarse + 1));
         HIPCHK(grow(ctx->d_ccur, ctx->ncoarse + 1));
-        HIPCHK(grow(ctx->d_csink, 4));
         HIPCHK(launch_zero32(ctx->s, ctx->d_ccnt.p, nc));
-        if (ctx->batch_cap) HIPCHK(grow(ctx->d_bins1, 2 * ctx->batch_cap));
     }
     if (ctx->opts.scatter_mode == CUPK_SCATTER_STAGED) {
         // counts: kCntGroups copies (one in use unless classify blocks also
@@ -1832,9 +1854,9 @@ int set_geometry(cupk_ctx *ctx, uint32_t tv, uint32_t rows, uint32_t chunk, uint
         HIPCHK(grow(ctx->d_tcur, ctx->ntiles + 1));
         // the scan kernel re-zeroes the counts after every batch
         HIPCHK(launch_zero32(ctx->s, ctx->d_tcnt.p, ncnt));
-        // work-item capacity depends on ntiles and chunk
-        const size_t icap = 2 * ctx->batch_cap / chunk + ctx->ntiles + 1;
-        HIPCHK(grow(ctx->d_items, 2 * icap));
+        // record width and work-item capacity depend on the geometry
+        const int rc = ensure_bins(ctx, ctx->batch_cap);
+        if (rc != CUPK_OK) return rc;
     }
     return ensure_rel(ctx);
 }

@@ -256,13 +256,19 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(uint32_t *__restrict
                         o += cg[g];
                     }
             }
-            for (uint32_t j = 0; j < k; j++) {
-                const uint32_t q = carry_i + ex_k + j;
-                if (q < items_cap) {
-                    items[2 * q] = t;
-                    items[2 * q + 1] = j;
-                }
-            }
+        }
+        // a thread lists the items of its tile, a wave those of a tile that
+        // has many
+        constexpr uint32_t kMany = 8;
+        auto list = [&](uint32_t tile, uint32_t first, uint32_t j) {
+            if (first + j < items_cap) ((uint2 *)items)[first + j] = make_uint2(tile, j);
+        };
+        if (k <= kMany)
+            for (uint32_t j = 0; j < k; j++) list(t, carry_i + ex_k, j);
+        for (uint64_t m = __ballot(k > kMany); m; m &= m - 1) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(m);
+            const uint32_t kl = __shfl(k, l), tl = __shfl(t, l), fl = __shfl(carry_i + ex_k, l);
+            for (uint32_t j = __lane_id(); j < kl; j += 64) list(tl, fl, j);
         }
         carry_r += tot_c;
         carry_i += tot_k;
@@ -919,9 +925,8 @@ hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc
 //    list of work items (tile, chunk) where a chunk is at most `chunk`
 //    records of one tile's bin.
 // 2. k_tile_fill: each update writes one record per endpoint into the bin
-//    of that endpoint's tile: u | v << 32, with bit 63 set (kRecV) in the
-//    record of v.  Slots are reserved per block in LDS first, so global
-//    atomics are per (block, tile), not per record.
+//    of that endpoint's tile (make_rec).  Slots are reserved per block in LDS
+//    first, so global atomics are per (block, tile), not per record.
 // 3. k_tile_scatter_stag (up to kStagMaxC columns) or k_tile_scatter: one
 //    work item per block iteration.  The block keeps a zeroed LDS delta of
 //    depth rows 0..rows-1 for the tile's vertices, XORs every (record,
@@ -930,15 +935,53 @@ hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc
 //    plain read-XOR-write when the item is the tile's whole bin (no other
 //    block touches these vertices), a device atomic XOR otherwise.
 // ---------------------------------------------------------------------------
-constexpr uint64_t kRecV = 1ull << 63;  // the record is for endpoint v
+
+// The record of endpoint w of an update {w, o} in a bin of 2^shift vertices.
+// The binning is bound by HBM, so records are 32 bits where that holds them:
+// w's place in the bin, then o (rec_wide otherwise).  The bin gives the rest
+// of w, and the update's two endpoints are told apart by their order.  Wide
+// records hold the update itself: u | v << 32 with u < v, bit 63 (kRecV) set
+// in the record of v.  6.7e7 updates in two levels (16-vertex tiles, V =
+// 2^20): 0.63 ms for the two fills and the count against 1.30 with wide ones
+// in items of 4,096 and 8,192 records.
+constexpr uint64_t kRecV = 1ull << 63;
+
+bool rec_wide(uint32_t V, uint32_t shift)
+{
+    return V > 1 && 32u - (uint32_t)__builtin_clz(V - 1) + shift > 32u;
+}
+
+template <class R>
+DEVI R make_rec(uint32_t w, uint32_t o, uint32_t shift)
+{
+    if constexpr (sizeof(R) == 4)
+        return (w & ((1u << shift) - 1)) | o << shift;
+    else
+        return w < o ? w | (uint64_t)o << 32 : o | (uint64_t)w << 32 | kRecV;
+}
+
+// w and o of a record in the bin whose first vertex is w0
+template <class R>
+DEVI void read_rec(R r, uint32_t w0, uint32_t shift, uint32_t &w, uint32_t &o)
+{
+    if constexpr (sizeof(R) == 4) {
+        w = w0 + ((uint32_t)r & ((1u << shift) - 1));
+        o = (uint32_t)r >> shift;
+    } else {
+        const uint32_t u = (uint32_t)r, v = (uint32_t)(r >> 32) & 0x7fffffffu;
+        w = r & kRecV ? v : u;
+        o = r & kRecV ? u : v;
+    }
+}
 
 constexpr uint32_t kFillThreads = 1024;
 constexpr uint32_t kFillPerBlock = 4096;
 constexpr uint32_t kFillPerThread = kFillPerBlock / kFillThreads;
 
+template <class R>
 __global__ __launch_bounds__(kFillThreads) void k_tile_fill(
     const BatchDesc *__restrict__ desc, BatchDesc dv, uint32_t V, uint32_t tile_shift,
-    uint32_t ntiles, uint32_t *__restrict__ cur, uint64_t *__restrict__ bins,
+    uint32_t ntiles, uint32_t *__restrict__ cur, R *__restrict__ bins,
     const uint32_t *__restrict__ hdr)
 {
     __shared__ uint32_t lcnt[kLdsHistMax];
@@ -962,9 +1005,8 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill(
             uint32_t u, v;
             bool del;
             unpack(p[k], V, u, v, del);
-            const uint64_t rec = (uint64_t)u | ((uint64_t)v << 32);
-            bins[atomicAdd(&cur[u >> tile_shift], 1u)] = rec;
-            bins[atomicAdd(&cur[v >> tile_shift], 1u)] = rec | kRecV;
+            bins[atomicAdd(&cur[u >> tile_shift], 1u)] = make_rec<R>(u, v, tile_shift);
+            bins[atomicAdd(&cur[v >> tile_shift], 1u)] = make_rec<R>(v, u, tile_shift);
         }
         return;
     }
@@ -995,34 +1037,36 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill(
         uint32_t u, v;
         bool del;
         unpack(p[k], V, u, v, del);
-        const uint64_t rec = (uint64_t)u | ((uint64_t)v << 32);
-        bins[lcnt[u >> tile_shift] + ru[k]] = rec;
-        bins[lcnt[v >> tile_shift] + rv[k]] = rec | kRecV;
+        bins[lcnt[u >> tile_shift] + ru[k]] = make_rec<R>(u, v, tile_shift);
+        bins[lcnt[v >> tile_shift] + rv[k]] = make_rec<R>(v, u, tile_shift);
     }
 }
 
 // Fill for up to kFillStageTiles tiles: the block's 2*kFillPerBlock records
 // are first counting-sorted by tile in LDS, then written out in that order,
 // so that the lanes of a wave store one (block, tile) run after another into
-// consecutive bin words (coalesced) instead of 8-byte words scattered over
-// all tiles.  Dynamic LDS: fill_stage_lds(ntiles) bytes.
+// consecutive bin words (coalesced) instead of single words scattered over
+// all tiles.  A 32-bit record's tile is staged beside it.  Dynamic LDS:
+// fill_stage_lds bytes.
 static_assert(kFillStageTiles == 2 * kFillThreads, "two tiles per fill thread");
-static size_t fill_stage_lds(uint32_t ntiles)
+static size_t fill_stage_lds(uint32_t ntiles, bool wide)
 {
-    return (size_t)2 * kFillPerBlock * 8 + (size_t)2 * ntiles * 4 + 160 * 4;
+    return (size_t)2 * kFillPerBlock * (wide ? 8 : 6) + (size_t)2 * ntiles * 4 + 160 * 4;
 }
 
+template <class R>
 __global__ __launch_bounds__(kFillThreads) void k_tile_fill_staged(
     const BatchDesc *__restrict__ desc, BatchDesc dv, uint32_t V, uint32_t tile_shift,
-    uint32_t ntiles, uint32_t *__restrict__ cur, uint64_t *__restrict__ bins,
+    uint32_t ntiles, uint32_t *__restrict__ cur, R *__restrict__ bins,
     const uint32_t *__restrict__ hdr, const uint32_t *__restrict__ goff,
     const uint32_t *__restrict__ rel)
 {
     extern __shared__ uint64_t fsm[];
-    uint64_t *stage = fsm;                                   // records in tile order
-    uint32_t *lcnt = (uint32_t *)(fsm + 2 * kFillPerBlock);  // per tile: count, then bin base
+    R *stage = (R *)fsm;                                     // records in tile order
+    uint32_t *lcnt = (uint32_t *)(stage + 2 * kFillPerBlock);  // per tile: count, then bin base
     uint32_t *lpre = lcnt + ntiles;                          // per tile: first stage slot
     uint32_t *sh = lpre + ntiles;                            // scan scratch (160 words)
+    uint16_t *stile = (uint16_t *)(sh + 160);                // 32-bit records: their tiles
     if (hdr[HDR_REJ]) return;
     const uint64_t *__restrict__ upd = desc ? desc->upd : dv.upd;
     const uint32_t n = desc ? desc->n : dv.n;
@@ -1075,15 +1119,26 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill_staged(
         uint32_t u, v;
         bool del;
         unpack(p[k], V, u, v, del);
-        const uint64_t rec = (uint64_t)u | ((uint64_t)v << 32);
-        stage[lpre[u >> tile_shift] + ru[k]] = rec;
-        stage[lpre[v >> tile_shift] + rv[k]] = rec | kRecV;
+        const uint32_t tu = u >> tile_shift, tv = v >> tile_shift;
+        const uint32_t ju = lpre[tu] + ru[k], jv = lpre[tv] + rv[k];
+        stage[ju] = make_rec<R>(u, v, tile_shift);
+        stage[jv] = make_rec<R>(v, u, tile_shift);
+        if constexpr (sizeof(R) == 4) {
+            stile[ju] = (uint16_t)tu;
+            stile[jv] = (uint16_t)tv;
+        }
     }
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < tot; j += blockDim.x) {
-        const uint64_t rec = stage[j];
-        const uint32_t e = (rec & kRecV) ? (uint32_t)(rec >> 32) & 0x7fffffffu : (uint32_t)rec;
-        const uint32_t t = e >> tile_shift;
+        const R rec = stage[j];
+        uint32_t t;
+        if constexpr (sizeof(R) == 4) {
+            t = stile[j];
+        } else {
+            uint32_t w, o;
+            read_rec(rec, 0, tile_shift, w, o);
+            t = w >> tile_shift;
+        }
         bins[lcnt[t] + (j - lpre[t])] = rec;
     }
 }
@@ -1091,142 +1146,191 @@ __global__ __launch_bounds__(kFillThreads) void k_tile_fill_staged(
 // ---------------------------------------------------------------------------
 // Two-level binning, for more tiles than one block's LDS histogram serves.
 // The classify kernel counts records per coarse bin (2^fshift consecutive
-// tiles) and the fill bins them by coarse bin into `bins1` (k_tile_fill_staged
-// on coarse bins).  Then every chunk of kFinePerBlock coarse-binned records
-// spans few tiles: k_fine_count counts the chunk's records per tile in LDS
-// and adds the counts to the tile counts (one global atomic per (chunk,
-// tile)), the multi-block tile scan turns them into bin offsets and work
-// items, and k_fine_fill ranks each chunk's records per tile in LDS,
-// reserves one range per (chunk, tile) from the tile's cursor and writes
-// the records there, staged in tile order in LDS so that each (chunk, tile)
-// run is written as consecutive words.  A tile more than kFineLdsTiles
-// (count) or kFillLdsTiles (fill) past the chunk's first coarse bin is
-// counted and reserved per record instead.
+// tiles), its scan lists work items (coarse bin, part of at most
+// fine_chunk records), and the fill bins the records by coarse bin into
+// `bins1` (k_tile_fill_staged on coarse bins).  k_fine_count counts an item's
+// records per tile in LDS and adds the counts to the tile counts (one global
+// atomic per (item, tile)), the multi-block tile scan turns them into bin
+// offsets and work items, and k_fine_fill ranks each item's records per tile
+// in LDS, reserves one range per (item, tile) from the tile's cursor and
+// writes the records there, staged in tile order in LDS so that each (item,
+// tile) run is written as consecutive words.  Bound by HBM: the items are as
+// large as the staged records leave LDS for two blocks of a CU, which keeps
+// the runs long and has few reservations and barriers per record.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kFineThreads = 1024;
-constexpr uint32_t kFinePer = 8;
-constexpr uint32_t kFinePerBlock = kFineThreads * kFinePer;
+template <class R>
+constexpr uint32_t kFinePer = sizeof(R) == 4 ? 16 : 8;  // records per thread
 
-DEVI uint32_t rec_endpoint(uint64_t rec)
+uint32_t fine_chunk(bool wide)
 {
-    return (rec & kRecV) ? (uint32_t)(rec >> 32) & 0x7fffffffu : (uint32_t)rec;
+    return kFineThreads * (wide ? kFinePer<uint64_t> : kFinePer<uint32_t>);
 }
 
+// Block b's item: consecutive items to the blocks of one XCD (blocks go round
+// robin over the 8 XCDs), whose L2 then joins the runs that neighbouring
+// items write next to each other.
+DEVI uint32_t fine_item(uint32_t b, uint32_t n)
+{
+    const uint32_t x = b % 8, q = n / 8, r = n % 8;
+    return x * q + min(x, r) + b / 8;
+}
+
+template <class R>
 __global__ __launch_bounds__(kFineThreads) void k_fine_count(
-    const uint64_t *__restrict__ bins1, const uint32_t *__restrict__ total, uint32_t tile_shift,
-    uint32_t fshift, uint32_t *__restrict__ cnt, const uint32_t *__restrict__ hdr)
-{
-    __shared__ uint32_t hist[kFineLdsTiles];
-    if (hdr[HDR_REJ]) return;
-    const uint32_t n = *total;
-    const uint32_t begin = blockIdx.x * kFinePerBlock;
-    if (begin >= n) return;
-    const uint32_t t_lo = (rec_endpoint(bins1[begin]) >> (tile_shift + fshift)) << fshift;
-    for (uint32_t j = threadIdx.x; j < kFineLdsTiles; j += kFineThreads) hist[j] = 0;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t k = 0; k < kFinePer; k++) {
-        const uint32_t i = begin + k * kFineThreads + threadIdx.x;
-        if (i >= n) continue;
-        const uint32_t t = rec_endpoint(bins1[i]) >> tile_shift;
-        if (t - t_lo < kFineLdsTiles)
-            atomicAdd(&hist[t - t_lo], 1u);
-        else
-            atomicAdd(&cnt[t], 1u);
-    }
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < kFineLdsTiles; j += kFineThreads) {
-        const uint32_t c = hist[j];
-        if (c) atomicAdd(&cnt[t_lo + j], c);
-    }
-}
-
-// The fill takes half as many records per block as the count, so that its
-// LDS (the block's records staged in tile order, and per tile the count,
-// stage start and reserved bin start) stays within 64 KiB.
-constexpr uint32_t kFillPer2 = 4;
-constexpr uint32_t kFillPerBlock2 = kFineThreads * kFillPer2;
-constexpr uint32_t kFillLdsTiles = 2 * kFineThreads;
-
-__global__ __launch_bounds__(kFineThreads) void k_fine_fill(
-    const uint64_t *__restrict__ bins1, const uint32_t *__restrict__ total, uint32_t tile_shift,
-    uint32_t fshift, uint32_t *__restrict__ cur, uint64_t *__restrict__ bins,
+    const R *__restrict__ bins1, const uint32_t *__restrict__ coff,
+    const uint32_t *__restrict__ citems, const uint32_t *__restrict__ ncitems,
+    uint32_t tile_shift, uint32_t fshift, uint32_t *__restrict__ cnt,
     const uint32_t *__restrict__ hdr)
 {
-    __shared__ uint64_t stage[kFillPerBlock2];  // local records in tile order
-    __shared__ uint32_t lcnt[kFillLdsTiles];    // per tile: count, then reserved bin start
-    __shared__ uint32_t lpre[kFillLdsTiles];    // per tile: first stage slot
-    __shared__ uint32_t sh[160];
-    if (hdr[HDR_REJ]) return;
-    const uint32_t n = *total;
-    const uint32_t begin = blockIdx.x * kFillPerBlock2;
-    if (begin >= n) return;
-    const uint32_t t_lo = (rec_endpoint(bins1[begin]) >> (tile_shift + fshift)) << fshift;
-    for (uint32_t j = threadIdx.x; j < kFillLdsTiles; j += kFineThreads) lcnt[j] = 0;
-    __syncthreads();
-    uint64_t rec[kFillPer2];
-    uint32_t rk[kFillPer2];  // rank in the block's share of its tile, or the final position
+    extern __shared__ uint32_t fine_sm[];
+    uint32_t *hist = fine_sm;  // per tile of the coarse bin
+    constexpr uint32_t P = kFinePer<R>;
+    const uint32_t nit = hdr[HDR_REJ] ? 0u : *ncitems;
+    if (blockIdx.x >= nit) return;
+    const uint32_t it = fine_item(blockIdx.x, nit);
+    const uint32_t bin = citems[2 * it];
+    const uint32_t cb = coff[bin] + citems[2 * it + 1] * (kFineThreads * P);
+    const uint32_t n = min(coff[bin + 1] - cb, kFineThreads * P);
+    const uint32_t T = 1u << fshift, t_lo = bin << fshift;
+    R rec[P];
 #pragma unroll
-    for (uint32_t k = 0; k < kFillPer2; k++) {
-        const uint32_t i = begin + k * kFineThreads + threadIdx.x;
-        rec[k] = i < n ? bins1[i] : 0;
-        rk[k] = 0;
-        if (i >= n) continue;
-        const uint32_t t = rec_endpoint(rec[k]) >> tile_shift;
-        rk[k] = t - t_lo < kFillLdsTiles ? atomicAdd(&lcnt[t - t_lo], 1u) : atomicAdd(&cur[t], 1u);
+    for (uint32_t k = 0; k < P; k++) {
+        const uint32_t i = k * kFineThreads + threadIdx.x;
+        rec[k] = i < n ? bins1[cb + i] : 0;
+    }
+    for (uint32_t t = threadIdx.x; t < T; t += kFineThreads) hist[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < P; k++) {
+        if (k * kFineThreads + threadIdx.x >= n) continue;
+        uint32_t w, o;
+        read_rec(rec[k], 0, tile_shift + fshift, w, o);
+        atomicAdd(&hist[(w >> tile_shift) & (T - 1)], 1u);
     }
     __syncthreads();
-    // stage starts (a block scan, two tiles per thread) and one reserved bin
-    // range per tile present in this block
-    const uint32_t t0 = 2 * threadIdx.x;
-    const uint32_t c0 = lcnt[t0], c1 = lcnt[t0 + 1];
-    uint32_t tot;
-    const uint32_t ex = block_exscan<kFineThreads>(c0 + c1, tot, sh);
-    lpre[t0] = ex;
-    lpre[t0 + 1] = ex + c0;
-    lcnt[t0] = c0 ? atomicAdd(&cur[t_lo + t0], c0) : 0u;
-    lcnt[t0 + 1] = c1 ? atomicAdd(&cur[t_lo + t0 + 1], c1) : 0u;
+    for (uint32_t t = threadIdx.x; t < T; t += kFineThreads) {
+        const uint32_t c = hist[t];
+        if (c) atomicAdd(&cnt[t_lo + t], c);
+    }
+}
+
+template <class R>
+static size_t fine_fill_lds(uint32_t fshift)
+{
+    return (size_t)kFineThreads * kFinePer<R> * sizeof(R) + ((size_t)8 << fshift);
+}
+
+template <class R, class R2>
+__global__ __launch_bounds__(kFineThreads, 8) void k_fine_fill(
+    const R *__restrict__ bins1, const uint32_t *__restrict__ coff,
+    const uint32_t *__restrict__ citems, const uint32_t *__restrict__ ncitems,
+    uint32_t tile_shift, uint32_t fshift, uint32_t *__restrict__ cur, R2 *__restrict__ bins,
+    const uint32_t *__restrict__ hdr)
+{
+    extern __shared__ uint32_t fine_sm[];
+    __shared__ uint32_t sh[160];
+    constexpr uint32_t P = kFinePer<R>;
+    const uint32_t nit = hdr[HDR_REJ] ? 0u : *ncitems;
+    if (blockIdx.x >= nit) return;
+    const uint32_t it = fine_item(blockIdx.x, nit);
+    const uint32_t bin = citems[2 * it];
+    const uint32_t cb = coff[bin] + citems[2 * it + 1] * (kFineThreads * P);
+    const uint32_t n = min(coff[bin + 1] - cb, kFineThreads * P);
+    const uint32_t cs = tile_shift + fshift;
+    const uint32_t T = 1u << fshift, t_lo = bin << fshift;
+    R *stage = (R *)fine_sm;                               // the item's records in tile order
+    uint32_t *lcnt = (uint32_t *)(stage + kFineThreads * P);  // per tile: count, then bin base
+    uint32_t *lpre = lcnt + T;                             // per tile: first stage slot
+    R rec[P];
+#pragma unroll
+    for (uint32_t k = 0; k < P; k++) {
+        const uint32_t i = k * kFineThreads + threadIdx.x;
+        rec[k] = i < n ? bins1[cb + i] : 0;
+    }
+    for (uint32_t t = threadIdx.x; t < T; t += kFineThreads) lcnt[t] = 0;
+    __syncthreads();
+    static_assert(kFineThreads * P < 65536, "two ranks per register");
+    uint32_t rk[P / 2];  // ranks in the item's shares of the records' tiles
+#pragma unroll
+    for (uint32_t k = 0; k < P; k++) {
+        uint32_t q = 0;
+        if (k * kFineThreads + threadIdx.x < n) {
+            uint32_t w, o;
+            read_rec(rec[k], 0, cs, w, o);
+            q = atomicAdd(&lcnt[(w >> tile_shift) & (T - 1)], 1u);
+        }
+        rk[k / 2] = k % 2 ? rk[k / 2] | q << 16 : q;
+    }
+    __syncthreads();
+    uint32_t carry = 0;
+    for (uint32_t t0 = 0; t0 < T; t0 += kFineThreads) {
+        const uint32_t t = t0 + threadIdx.x;
+        const uint32_t c = t < T ? lcnt[t] : 0u;
+        uint32_t tot;
+        const uint32_t ex = carry + block_exscan<kFineThreads>(c, tot, sh);
+        carry += tot;
+        if (t < T) {
+            lpre[t] = ex;
+            // (mod 2^32) stage slot j of the tile goes to word lcnt + j
+            if (c) lcnt[t] = atomicAdd(&cur[t_lo + t], c) - ex;
+        }
+    }
     __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kFillPer2; k++) {
-        const uint32_t i = begin + k * kFineThreads + threadIdx.x;
-        if (i >= n) continue;
-        const uint32_t t = rec_endpoint(rec[k]) >> tile_shift;
-        if (t - t_lo < kFillLdsTiles)
-            stage[lpre[t - t_lo] + rk[k]] = rec[k];
-        else
-            bins[rk[k]] = rec[k];
+    for (uint32_t k = 0; k < P; k++) {
+        if (k * kFineThreads + threadIdx.x >= n) continue;
+        uint32_t w, o;
+        read_rec(rec[k], 0, cs, w, o);
+        const uint32_t q = k % 2 ? rk[k / 2] >> 16 : rk[k / 2] & 0xffffu;
+        stage[lpre[(w >> tile_shift) & (T - 1)] + q] = rec[k];
     }
     __syncthreads();
     // out in tile order: the lanes of a wave store runs of consecutive words
-    for (uint32_t j = threadIdx.x; j < tot; j += kFineThreads) {
-        const uint64_t r = stage[j];
-        const uint32_t t = (rec_endpoint(r) >> tile_shift) - t_lo;
-        bins[lcnt[t] + (j - lpre[t])] = r;
+    for (uint32_t j = threadIdx.x; j < n; j += kFineThreads) {
+        uint32_t w, o;
+        read_rec(stage[j], 0, cs, w, o);
+        R2 out;
+        if constexpr (sizeof(R) == 8 && sizeof(R2) == 8)
+            out = stage[j];
+        else
+            out = make_rec<R2>(w, o, tile_shift);
+        bins[lcnt[(w >> tile_shift) & (T - 1)] + j] = out;
     }
 }
 
-hipError_t launch_fine(hipStream_t s, uint32_t grid_n, const uint32_t *hdr, const uint64_t *bins1,
-                       const uint32_t *total, uint32_t tile_shift, uint32_t fshift,
-                       uint32_t ntiles, uint32_t *tile_cnt, const ScanArgs &sa, uint64_t *bins)
+hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_t *hdr,
+                       const uint32_t *bins1, const uint32_t *coff, const uint32_t *citems,
+                       const uint32_t *ncitems, uint32_t tile_shift, uint32_t fshift,
+                       uint32_t ntiles, uint32_t *tile_cnt, const ScanArgs &sa, uint32_t *bins)
 {
     if (grid_n == 0) return hipSuccess;
     if (!sa.sums || sa.groups != 1 || fshift == 0 || (1u << fshift) > kFineLdsTiles)
         return hipErrorInvalidValue;
-    const uint32_t nb = (uint32_t)((2 * (uint64_t)grid_n + kFinePerBlock - 1) / kFinePerBlock);
-    k_fine_count<<<nb, kFineThreads, 0, s>>>(bins1, total, tile_shift, fshift, tile_cnt, hdr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint32_t nch = tile_scan_chunks(ntiles);
-    k_tile_sums<<<nch, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa.chunk, sa.sums);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_tile_offsets<<<nch, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa, hdr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint32_t nf = (uint32_t)((2 * (uint64_t)grid_n + kFillPerBlock2 - 1) / kFillPerBlock2);
-    k_fine_fill<<<nf, kFineThreads, 0, s>>>(bins1, total, tile_shift, fshift, sa.cur, bins, hdr);
-    return hipGetLastError();
+    const uint32_t ncoarse = (ntiles + (1u << fshift) - 1) >> fshift;
+    auto go = [&](auto *b1, auto *b2) {
+        using R = std::remove_pointer_t<decltype(b1)>;
+        using R2 = std::remove_pointer_t<decltype(b2)>;
+        const uint32_t nb = (uint32_t)(2 * (uint64_t)grid_n / fine_chunk(sizeof(R) == 8)) + ncoarse;
+        k_fine_count<R><<<nb, kFineThreads, (size_t)4 << fshift, s>>>(
+            b1, coff, citems, ncitems, tile_shift, fshift, tile_cnt, hdr);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const uint32_t nch = tile_scan_chunks(ntiles);
+        k_tile_sums<<<nch, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa.chunk, sa.sums);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k_tile_offsets<<<nch, kScanThreads, 0, s>>>(tile_cnt, ntiles, sa, hdr);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k_fine_fill<R, R2><<<nb, kFineThreads, fine_fill_lds<R>(fshift), s>>>(
+            b1, coff, citems, ncitems, tile_shift, fshift, sa.cur, b2, hdr);
+        return hipGetLastError();
+    };
+    uint32_t *b1 = const_cast<uint32_t *>(bins1);
+    if (!rec_wide(V, tile_shift + fshift)) return go(b1, bins);
+    if (!rec_wide(V, tile_shift)) return go((uint64_t *)b1, bins);
+    return go((uint64_t *)b1, (uint64_t *)bins);
 }
 
 // ---------------------------------------------------------------------------
@@ -1308,7 +1412,7 @@ constexpr uint32_t kStagFew = 2 * (kStagThreads / C);
 
 template <uint32_t C>
 __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_stag(
-    DevSketch sk, const uint64_t *__restrict__ bins, const uint32_t *__restrict__ off,
+    DevSketch sk, const uint32_t *__restrict__ bins, const uint32_t *__restrict__ off,
     const uint32_t *__restrict__ items, const uint32_t *__restrict__ nitems_p, uint32_t tile_shift,
     uint32_t rows, uint32_t chunk, const uint32_t *__restrict__ hdr,
     unsigned long long *__restrict__ touched)
@@ -1367,7 +1471,7 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
     };
     range(j);
     uint32_t r = cb + (ce - cb <= kStagFew<C> ? few_i : threadIdx.x);
-    uint64_t rec = r < ce ? bins[r] : 0;
+    uint32_t rec = r < ce ? bins[r] : 0;
     while (it < nitems) {
         const bool single = re - rb <= chunk;
         const uint32_t w0 = tile << tile_shift;
@@ -1386,11 +1490,10 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
         if (ce - cb <= kStagFew<C>) {
             const uint64_t seed1 = seedt[s];
             while (r < ce && few_i < kStagThreads / C) {
-                const uint32_t u = (uint32_t)rec, v = (uint32_t)(rec >> 32) & 0x7fffffffu;
-                const uint32_t vl = ((rec & kRecV) ? v : u) - w0;
+                const uint32_t vl = rec & (TV - 1), w = w0 + vl, o = rec >> tile_shift;
                 r += kStagThreads / C;
                 if (r < ce) rec = bins[r];
-                const uint64_t x = (uint64_t)u * V + v;
+                const uint64_t x = (uint64_t)min(w, o) * V + max(w, o);
                 const uint64_t z = mix64_mid(mix64_head(x) ^ seed1);
                 const uint32_t d0 = (uint32_t)__builtin_ctz(mix64_low(z) | stop);
                 const LdsWords p = L + (vl * VS + d0 * RS + s);
@@ -1412,11 +1515,10 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
                 seed1[t] = seedt[s + t];
             });
             while (r < ce) {
-                const uint32_t u = (uint32_t)rec, v = (uint32_t)(rec >> 32) & 0x7fffffffu;
-                const uint32_t vl = ((rec & kRecV) ? v : u) - w0;
+                const uint32_t vl = rec & (TV - 1), w = w0 + vl, o = rec >> tile_shift;
                 r += kStagThreads;
                 if (r < ce) rec = bins[r];  // in flight while this one is hashed
-                const uint64_t x = (uint64_t)u * V + v;
+                const uint64_t x = (uint64_t)min(w, o) * V + max(w, o);
                 const uint64_t y = mix64_head(x);
                 const uint32_t a0 = lbase + __umul24(vl, VS * 8) + s * 8, a1 = a0 - C * 8;
                 uint32_t deep = 0;  // bit C-1-t: the t-th column's depth is >= rows
@@ -1576,7 +1678,7 @@ DEVI void tile_pair(uint8_t *lds8, uint32_t RSB, uint32_t pg, uint32_t rows, uin
     }
 }
 
-// More than kStagMaxC columns (or more than 31 rows).  One (record, column)
+// More than kStagMaxC columns, more than 31 rows, or wide records.  One (record, column)
 // pair per lane: the edge index x = u*V + v of the record's update is hashed
 // for column c and (x, h) is XOR-ed into bucket (d, c) of its endpoint.  Lane l of a wave takes column l mod C of
 // record l / C (G = 64 / C records per wave step, lanes l >= G*C idle), so
@@ -1589,8 +1691,9 @@ DEVI void tile_pair(uint8_t *lds8, uint32_t RSB, uint32_t pg, uint32_t rows, uin
 // touched (may be null) receives the number of buckets the launch changes
 // in HBM: folded buckets with a nonzero delta, plus one per pair that goes
 // to a deep row directly.
+template <class R>
 __global__ __launch_bounds__(kTileThreads) void k_tile_scatter(
-    DevSketch sk, const uint64_t *__restrict__ bins, const uint32_t *__restrict__ off,
+    DevSketch sk, const R *__restrict__ bins, const uint32_t *__restrict__ off,
     const uint32_t *__restrict__ items, const uint32_t *__restrict__ nitems_p, uint32_t tile_shift,
     uint32_t rows, uint32_t chunk, const uint32_t *__restrict__ hdr,
     unsigned long long *__restrict__ touched)
@@ -1636,11 +1739,11 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_scatter(
             const uint32_t ns = min(kTileStage, ce - sb);
             // stage: decode each record once
             for (uint32_t i = threadIdx.x; i < ns; i += kTileThreads) {
-                const uint64_t rec = bins[sb + i];
-                const uint32_t u = (uint32_t)rec, v = (uint32_t)(rec >> 32) & 0x7fffffffu;
-                const uint32_t vl = ((rec & kRecV) ? v : u) - w0;
+                uint32_t w, o;
+                read_rec(bins[sb + i], w0, tile_shift, w, o);
+                const uint32_t vl = w - w0;
                 StagedRec r;
-                r.x = (uint64_t)u * V + v;
+                r.x = (uint64_t)min(w, o) * V + max(w, o);
                 r.y = mix64_head(r.x);
                 r.qb = __umul24(vl, C) * 8;
                 r.vl = vl;
@@ -1703,7 +1806,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_scatter(
 
 hipError_t launch_bin(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32_t grid_n,
                       DevSketch sk, const uint32_t *hdr, const StagedParams &p,
-                      uint32_t *tile_cur, uint64_t *bins, const uint32_t *tile_goff,
+                      uint32_t *tile_cur, uint32_t *bins, const uint32_t *tile_goff,
                       const uint32_t *tile_rel)
 {
     if (grid_n == 0) return hipSuccess;
@@ -1714,13 +1817,18 @@ hipError_t launch_bin(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32
     static_assert(kRelMaxTiles <= kFillStageTiles && kRelMaxTiles <= kLdsHistMax,
                   "tile_rel needs the classify's LDS counts and the staged fill");
     if (tile_rel && (p.ntiles > kRelMaxTiles || !tile_goff)) return hipErrorInvalidValue;
-    if (p.ntiles <= kFillStageTiles)
-        k_tile_fill_staged<<<fb, kFillThreads, fill_stage_lds(p.ntiles), s>>>(
-            desc, dv, sk.V, p.tile_shift, p.ntiles, tile_cur, bins, hdr, tile_goff, tile_rel);
-    else
-        k_tile_fill<<<fb, kFillThreads, 0, s>>>(desc, dv, sk.V, p.tile_shift, p.ntiles, tile_cur,
-                                                bins, hdr);
-    return hipGetLastError();
+    auto go = [&](auto *b) {
+        using R = std::remove_pointer_t<decltype(b)>;
+        if (p.ntiles <= kFillStageTiles)
+            k_tile_fill_staged<R>
+                <<<fb, kFillThreads, fill_stage_lds(p.ntiles, sizeof(R) == 8), s>>>(
+                    desc, dv, sk.V, p.tile_shift, p.ntiles, tile_cur, b, hdr, tile_goff, tile_rel);
+        else
+            k_tile_fill<R><<<fb, kFillThreads, 0, s>>>(desc, dv, sk.V, p.tile_shift, p.ntiles,
+                                                       tile_cur, b, hdr);
+        return hipGetLastError();
+    };
+    return rec_wide(sk.V, p.tile_shift) ? go((uint64_t *)bins) : go(bins);
 }
 
 // f(integral_constant<uint32_t, C - 1>) for C = 1 .. kStagMaxC (host)
@@ -1736,14 +1844,15 @@ static void for_columns(F &f)
 }
 
 hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const StagedParams &p,
-                       const uint32_t *tile_off, const uint64_t *bins, const uint32_t *items,
+                       const uint32_t *tile_off, const uint32_t *bins, const uint32_t *items,
                        const uint32_t *nitems, unsigned long long *touched)
 {
     const size_t delta = (size_t)2 * p.rows * sk.C * (1u << p.tile_shift) * sizeof(uint64_t);
     if (!tile_geometry_fits(p.rows, sk.C, 1u << p.tile_shift, p.layout))
         return hipErrorInvalidValue;
     const uint32_t rfast = min(p.rows, sk.D - 1);
-    if (sk.C <= kStagMaxC && rfast <= 31) {
+    const bool wide = rec_wide(sk.V, p.tile_shift);
+    if (sk.C <= kStagMaxC && rfast <= 31 && !wide) {
         const size_t lds = ((size_t)(rfast + 1) * sk.C * 16 << p.tile_shift) + (size_t)sk.C * 16;
         if (lds > kCuLds) return hipErrorInvalidValue;
         // Dense batches (64 records per vertex and more) have heavy items:
@@ -1770,8 +1879,13 @@ hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const S
     // Persistent grid: a few blocks per CU, each looping over work items.
     const uint32_t grid = min(p.items_cap, p.grid ? p.grid : 256u * 8u);
     const size_t lds = delta + (size_t)kTileStage * kStagedRecBytes;
-    k_tile_scatter<<<grid, kTileThreads, lds, s>>>(sk, bins, tile_off, items, nitems, p.tile_shift,
-                                                   p.rows, p.chunk, hdr, touched);
+    if (wide)
+        k_tile_scatter<<<grid, kTileThreads, lds, s>>>(sk, (const uint64_t *)bins, tile_off, items,
+                                                       nitems, p.tile_shift, p.rows, p.chunk, hdr,
+                                                       touched);
+    else
+        k_tile_scatter<<<grid, kTileThreads, lds, s>>>(sk, bins, tile_off, items, nitems,
+                                                       p.tile_shift, p.rows, p.chunk, hdr, touched);
     return hipGetLastError();
 }
 

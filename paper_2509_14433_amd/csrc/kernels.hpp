@@ -207,26 +207,32 @@ hipError_t launch_scatter_atomic(hipStream_t s, const BatchDesc *desc, BatchDesc
 // incremented by the number of buckets the launch changes in HBM.
 hipError_t launch_bin(hipStream_t s, const BatchDesc *desc, BatchDesc dv, uint32_t grid_n,
                       DevSketch sk, const uint32_t *hdr, const StagedParams &p,
-                      uint32_t *tile_cur, uint64_t *bins, const uint32_t *tile_goff,
+                      uint32_t *tile_cur, uint32_t *bins, const uint32_t *tile_goff,
                       const uint32_t *tile_rel);
 hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const StagedParams &p,
-                       const uint32_t *tile_off, const uint64_t *bins, const uint32_t *items,
+                       const uint32_t *tile_off, const uint32_t *bins, const uint32_t *items,
                        const uint32_t *nitems, unsigned long long *touched);
+// Whether the records of bins of 2^shift vertices take 64 bits: two words of
+// bins per record instead of one.
+bool rec_wide(uint32_t V, uint32_t shift);
 // Second level of the two-level binning (used when there are more tiles
 // than kFillStageTiles): bins1 holds the batch's records binned by coarse
 // bin (2^fshift tiles each; the classify kernel counted them and the fill
-// wrote them), total points at their number (the coarse scan's last
-// offset).  Counts them per tile into tile_cnt, scans with the multi-block
-// tile scan into sa (one count copy, sa.sums set) and writes them into
-// their tile bins in `bins`.
+// wrote them) at the coarse scan's offsets coff, and citems its work items
+// (coarse bin, part of at most fine_chunk(rec_wide(V, tile_shift + fshift))
+// records), *ncitems of them.  Counts the records per tile into tile_cnt,
+// scans with the multi-block tile scan into sa (one count copy, sa.sums set)
+// and writes them into their tile bins in `bins`.
 constexpr uint32_t kFillStageTiles = 2048;
 // Most bins the classify kernel counts in LDS (beyond, with device atomics),
 // and most tiles per coarse bin (launch_fine).
 constexpr uint32_t kLdsHistMax = 8192;
 constexpr uint32_t kFineLdsTiles = 8192;
-hipError_t launch_fine(hipStream_t s, uint32_t grid_n, const uint32_t *hdr, const uint64_t *bins1,
-                       const uint32_t *total, uint32_t tile_shift, uint32_t fshift,
-                       uint32_t ntiles, uint32_t *tile_cnt, const ScanArgs &sa, uint64_t *bins);
+uint32_t fine_chunk(bool wide);
+hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_t *hdr,
+                       const uint32_t *bins1, const uint32_t *coff, const uint32_t *citems,
+                       const uint32_t *ncitems, uint32_t tile_shift, uint32_t fshift,
+                       uint32_t ntiles, uint32_t *tile_cnt, const ScanArgs &sa, uint32_t *bins);
 // Whether a staged-scatter geometry fits one block's LDS: the delta of
 // `rows` depth rows x C columns x tv vertices (alpha and gamma), plus, in
 // the pair layout, room to stage one block's worth of decoded records.
