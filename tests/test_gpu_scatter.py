@@ -82,6 +82,37 @@ def test_staged_scatter_edges(cupk, V, n, C, D, kw):
     ctx.close()
 
 
+WIDTHS = [
+    # V, edges, C, tile_vertices: where a vertex id and a place in a bin take
+    # 32 bits (records of one word) and where they take more (of two words)
+    (1 << 20, 300_000, 2, 16),        # 32 bits in the coarse bins
+    ((1 << 20) + 9, 300_000, 2, 16),  # 34 in the coarse bins, 25 in the tiles
+    (1 << 22, 40_000, 1, 1024),       # 38 in the coarse bins, 32 in the tiles
+    ((1 << 22) + 1, 40_000, 1, 1024),  # 39, 33
+    (1 << 21, 300_000, 2, 2048),      # one level: 32
+    ((1 << 21) + 5, 300_000, 2, 2048),  # one level: 33
+]
+
+
+@pytest.mark.parametrize("V,n,C,tv", WIDTHS)
+def test_record_widths(cupk, V, n, C, tv):
+    S = 0x3BD + tv
+    D = 3
+    u, v = _edges(V, n, V + C)
+    # half of them at the last vertices: the largest places and ids, long bins
+    u[::2] = V - 1 - u[::2] % 40
+    v[::2] = v[::2] % (V - 50)
+    print(f"widths V={V} n={len(u)} C={C} tv={tv}", flush=True)
+    ctx = cupk.Context(V, C, D, S, tile_vertices=tv, lds_rows=1,
+                       tile_layout=cupk.LAYOUT_RECORD)
+    ref = oracle.Sketch(V, C, D, S)
+    ctx.apply_updates(u, v, np.zeros(len(u), np.uint8))
+    ref.apply(u, v)
+    a, g = ctx.get_sketch()
+    assert np.array_equal(a, ref.alpha) and np.array_equal(g, ref.gamma)
+    ctx.close()
+
+
 DIRECT = [
     # V, edges, C, D: within the direct scatter's range; 16,384 and 16,385 on
     # either side of the one-block classification, a star, many and few columns
