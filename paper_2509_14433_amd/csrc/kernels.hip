@@ -1344,9 +1344,11 @@ hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_
 // words, and the LDS serializes atomics to one word (a 64-lane ds_xor_b64 on
 // one word takes 128 clocks per CU, on 64 words 7, on a staggered wave 8-11).
 //
-// What bounds it.  Dense batches: VALU issue, about 20 instructions per
-// (record, column), and the two LDS atomics beside them (about 20 clocks of
-// the CU's LDS).  Against one lane per (record, column) pair the record is
+// What bounds it.  Dense batches: VALU issue (busy all the time), 19
+// instructions per (record, column), 8 of them the two 64-bit products.  The
+// two LDS atomics beside them keep the LDS busy for 80% of the time; fewer bank
+// conflicts (rows padded to 16 words: 8 clocks per atomic instead of 10)
+// changed nothing.  Against one lane per (record, column) pair the record is
 // decoded once instead of read back from LDS (24 B) by each of its C lanes,
 // no lane idles (64 mod C did), the column seeds are C registers, the column
 // offset is the instruction's offset field, and the finalizer's last step
@@ -1357,10 +1359,11 @@ hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_
 // before their stores, clears the delta as it reads it, and the next item's
 // descriptor and first records are loaded under the current item.
 //
-// Deep pairs (depth >= rows; odds 2^-rows each) take no branch: they fall
-// into one extra LDS row that is never folded, a bit per column records
-// them, and the lane hashes them again after its columns and sends them to
-// HBM with device atomics.
+// Deep pairs (depth >= rows; odds 2^-rows each) fall into one extra LDS row
+// that is never folded, and after every two columns the wave branches if it
+// has one, to send it to HBM with device atomics.  Against a bit per column
+// and a loop over them after the columns, which hashed them again: 1.75 ms
+// instead of 1.82 for 1.3e8 records on 131,072 of 2^20 vertices, C = 20.
 //
 // Measured on one MI355X (records, vertices, C: this kernel / the pair
 // layout / one lane per record without the stagger, each at its best tile):
@@ -1431,6 +1434,7 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
     const uint32_t words = VS << tile_shift;
     const uint64_t DC2 = (uint64_t)D * C * 2;  // words per vertex in HBM
     const uint32_t stop = 1u << rfast;
+    const uint32_t deep = rows == D ? 64u : rfast;  // depth of a deep pair in LDS (64: none)
     const uint32_t nitems = err ? 0u : *nitems_p;
     const uint32_t s = threadIdx.x % C;        // first column of this lane
     const uint32_t few_i = threadIdx.x / C;    // its record in an item of few records
@@ -1502,7 +1506,7 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
                 const LdsWords p = L + (vl * VS + d0 * RS + s);
                 lds_xor(p, x);
                 lds_xor(p + C, z);
-                if (d0 == rfast && rows != D) {
+                if (d0 == deep) {
                     const uint64_t h = z ^ (z >> 31);
                     uint64_t *bp =
                         sk.b + (uint64_t)(w0 + vl) * DC2 + 2 * (depth_of(h, D) * C + s);
@@ -1524,41 +1528,46 @@ __global__ __launch_bounds__(kStagThreads, C <= 20 ? 6 : 4) void k_tile_scatter_
                 const uint64_t x = (uint64_t)min(w, o) * V + max(w, o);
                 const uint64_t y = mix64_head(x);
                 const uint32_t a0 = lbase + __umul24(vl, VS * 8) + s * 8, a1 = a0 - C * 8;
-                uint32_t deep = 0;  // bit C-1-t: the t-th column's depth is >= rows
-                static_for<0, C>([&](auto tt) {
-                    constexpr uint32_t t = decltype(tt)::value;
-                    const uint64_t z = mix64_mid(y ^ seed1[t]);
-                    const uint32_t d0 = (uint32_t)__builtin_ctz(mix64_low(z) | stop);
-                    uint32_t a = a0;
-                    if (t > 0)
-                        asm("v_cndmask_b32_e64 %0, %1, %2, %3"
-                            : "=v"(a)
-                            : "v"(a0), "v"(a1), "s"(wrap[t]));
-                    const LdsWords p = (LdsWords)(__umul24(d0, RS * 8) + a) + t;
-                    lds_xor(p, x);
-                    lds_xor(p + C, z);
-                    asm("v_cmp_eq_u32_e32 vcc, %1, %2\n\t"
-                        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-                        : "+v"(deep)
-                        : "s"(rfast), "v"(d0)
-                        : "vcc");
+                // columns t and t + 1 (t + 1 < C) of the record
+                auto columns = [&](auto tt) {
+                    constexpr uint32_t t = decltype(tt)::value * 2;
+                    constexpr uint32_t N = t + 1 < C ? 2 : 1;
+                    uint64_t z[2];
+                    uint32_t d0[2];
+                    static_for<0, N>([&](auto kk) {
+                        constexpr uint32_t k = decltype(kk)::value;
+                        z[k] = mix64_mid(y ^ seed1[t + k]);
+                        d0[k] = (uint32_t)__builtin_ctz(mix64_low(z[k]) | stop);
+                        uint32_t a = a0;
+                        if (t + k > 0)
+                            asm("v_cndmask_b32_e64 %0, %1, %2, %3"
+                                : "=v"(a)
+                                : "v"(a0), "v"(a1), "s"(wrap[t + k]));
+                        const LdsWords p = (LdsWords)(__umul24(d0[k], RS * 8) + a) + t + k;
+                        lds_xor(p, x);
+                        lds_xor(p + C, z[k]);
+                    });
+                    if (d0[0] == deep || (N > 1 && d0[1] == deep)) {
+                        static_for<0, N>([&](auto kk) {
+                            constexpr uint32_t k = decltype(kk)::value;
+                            if (d0[k] != deep) return;
+                            uint32_t c = s;
+                            asm volatile("" : "+v"(c));  // (not a register per column)
+                            c += t + k;
+                            if (c >= C) c -= C;
+                            const uint64_t h = z[k] ^ (z[k] >> 31);
+                            uint64_t *bp = sk.b + (uint64_t)(w0 + vl) * DC2 +
+                                           2 * (depth_of(h, D) * C + c);
+                            gxor(bp, x);
+                            gxor(bp + 1, h);
+                            nchanged++;
+                        });
+                    }
                     // keep the unrolled columns in order: interleaving all of
                     // them takes 60 more registers
-                    if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-                });
-                if (rows == D) deep = 0;  // the last row is a row like the others
-                while (deep) {
-                    const uint32_t b = 31u - (uint32_t)__builtin_clz(deep);
-                    deep &= ~(1u << b);
-                    uint32_t c = s + (C - 1 - b);
-                    if (c >= C) c -= C;
-                    const uint64_t h = mix64(x ^ sk.seeds[c]);
-                    uint64_t *bp =
-                        sk.b + (uint64_t)(w0 + vl) * DC2 + 2 * (depth_of(h, D) * C + c);
-                    gxor(bp, x);
-                    gxor(bp + 1, h);
-                    nchanged++;
-                }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                static_for<0, (C + 1) / 2>(columns);
             }
         }
         // the next item's first records, in flight during the fold
