@@ -94,7 +94,7 @@ DEVI void lxor(uint64_t *p, uint64_t v)
 // kernel is bound by the latency of those dependent loads and by the requests
 // that they make to L2.  The launch bound holds it at 78 registers (three
 // blocks per CU) where the compiler takes 235 (one block) by itself: 6.7e7
-// inserts at V = 2^20 in 0.26 ms instead of 0.44, 1.5e6 deletes at V =
+// inserts at V = 2^20 in 0.26 ms instead of 0.44, 3.0e6 deletes at V =
 // 200,003 in 37 us instead of 53.  The block writes its flagged updates in
 // stream order into its own region of the flag buffers (same offsets), at
 // positions from one prefix over (step, wave) counts; cnt[b] gets their
@@ -1372,6 +1372,8 @@ hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_
 //   2.0e6 on 16,384, C = 14:                  0.033 / 0.041 / 0.046 ms
 //   6.0e6 on 200,003, C = 18:                 0.252 / 0.260 / 0.260 ms
 //   2.0e5 on 131,072, C = 17:                 0.058 / 0.073 / 0.084 ms
+// (with 64-bit records and before the two changes below; 0.238 ms for the
+// fourth after them)
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) uint64_t *LdsWords;
 DEVI void lds_xor(LdsWords p, uint64_t v)
@@ -1407,7 +1409,7 @@ constexpr uint32_t kStagWaves = kStagThreads / 64;
 // Buckets a lane folds at a time.  Their loads are issued together, without a
 // branch between them (lanes with nothing to fold load the tile's first
 // bucket): behind branches the compiler waits for each load before the next.
-// 3.0e6 records on 200,003 vertices, C = 18: 0.238 instead of 0.247 ms, where
+// 6.0e6 records on 200,003 vertices, C = 18: 0.238 instead of 0.247 ms, where
 // reading and writing the first 7 to 9 of 36 depth rows of every vertex takes
 // 0.19 to 0.26 by itself; 4 or 6 buckets at a time are no faster.
 constexpr uint32_t kStagFold = 3;
