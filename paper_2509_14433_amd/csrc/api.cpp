@@ -256,6 +256,10 @@ static int reduce_sets(cupk_ctx *ctx, int slot, const std::vector<uint32_t> &vme
     a.tick = ctx->d_tick.p;
     a.canon = query ? nullptr : canon;
     a.res = !query ? nullptr : pub ? ctx->h_res.p : ctx->d_res.p;
+    if (nitems == 1) {
+        std::copy(h + nmem, h + nmem + 4, a.one);
+        std::copy(h, h + nmem, a.mem);
+    }
     if (pub) {
         a.seq_out = ctx->h_pub;
         a.seq = ++ctx->pub_seq;

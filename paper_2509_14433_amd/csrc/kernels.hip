@@ -2104,13 +2104,19 @@ __global__ __launch_bounds__(NG *kRedThreads) void k_reduce_sample(ReduceArgs a)
         uint32_t set = it, n = 1, parts = 1;
         bool frag = false;
         if (a.items) {
-            // one wave fetches the item and its members (host memory, maybe)
+            // one wave fetches the item and its members (host memory, maybe;
+            // an only item comes in the arguments: two reads over the host
+            // link, one after the other, less, 2 of 39 us for the cut of 37
+            // vertices)
             if (threadIdx.x < 64) {
                 uint32_t w = 0;
-                if (threadIdx.x < 4) w = a.items[4 * it + threadIdx.x];
+                const uint32_t *item = a.nitems == 1 ? a.one : a.items + 4 * it;
+                if (threadIdx.x < 4) w = item[threadIdx.x];
                 const uint32_t b = __shfl(w, 1), e = __shfl(w, 2);
                 if (threadIdx.x < 4) s_item[threadIdx.x] = w;
-                if (threadIdx.x < e - b) s_mem[threadIdx.x] = a.idx[b + threadIdx.x];
+                if (threadIdx.x < e - b)
+                    s_mem[threadIdx.x] =
+                        a.nitems == 1 ? a.mem[threadIdx.x] : a.idx[b + threadIdx.x];
             }
             __syncthreads();
             set = s_item[0];

@@ -261,6 +261,9 @@ struct ReduceArgs {
     int32_t *res;     // (status, u, v) per set, or null; device or pinned host memory
     uint32_t *seq_out;  // null, or where to publish seq once all is written
     uint32_t seq;
+    // an only item (items set, nitems 1) and its members, read instead of
+    // items and idx (launch_reduce_sample)
+    uint32_t one[4], mem[kRedChunk];
 };
 // zero_list: the sets of several items (nzero of them), whose aggregates and
 // tickets are zeroed first.  Every set must have an item (an empty one for an
