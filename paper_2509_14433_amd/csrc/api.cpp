@@ -101,10 +101,15 @@ int harvest_timers(cupk_ctx *ctx, bool all)
 // it, before it touches the forest again.
 constexpr uint32_t kLoadDirect = 1u << 16;
 
+static bool upload_due(const cupk_ctx *ctx)
+{
+    return ctx->forest_dev_stale || ctx->pages_pending;
+}
+
 int upload_forest_on(cupk_ctx *ctx, hipStream_t st)
 {
-    if (!ctx->forest_dev_stale) return CUPK_OK;
-    ctx->forest_dev_stale = false;
+    if (!upload_due(ctx)) return CUPK_OK;
+    ctx->forest_dev_stale = ctx->pages_pending = false;
     std::vector<uint32_t> &pg = ctx->up_pages;
     pg.clear();
     ctx->forest.take_pages(pg);
@@ -132,6 +137,28 @@ int upload_forest_on(cupk_ctx *ctx, hipStream_t st)
 }
 
 int upload_forest(cupk_ctx *ctx) { return upload_forest_on(ctx, ctx->s); }
+
+// The same for a pass that one block classifies: a short list of written
+// vertices goes along with it (*nd of them in h_delta; the classification
+// reads no block labels, their pages wait for the next upload), which saves
+// the upload's launch.
+static int delta_forest(cupk_ctx *ctx, uint32_t *nd)
+{
+    *nd = 0;
+    if (!ctx->forest_dev_stale) return CUPK_OK;
+    std::vector<uint32_t> &w = ctx->up_pages;
+    if (!ctx->forest.take_written(w)) return upload_forest(ctx);
+    HIPCHK(grow(ctx->h_delta, 3 * cupk::Forest::kMaxWritten, hipHostMallocCoherent));
+    for (size_t i = 0; i < w.size(); i++) {
+        ctx->h_delta.p[3 * i] = w[i];
+        ctx->h_delta.p[3 * i + 1] = ctx->h_lbl[w[i]];
+        ctx->h_delta.p[3 * i + 2] = ctx->h_par[w[i]];
+    }
+    *nd = (uint32_t)w.size();
+    ctx->forest_dev_stale = false;
+    ctx->pages_pending = true;
+    return CUPK_OK;
+}
 
 // One replacement-search set: a tree of the forest, reduced either from its
 // vertices or from fragment sketches of the previous round.
@@ -1300,10 +1327,6 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert, 
     int rc = harvest_timers(ctx, false);
     if (rc != CUPK_OK) return rc;
     ctx->flags_packed = false;
-    if (!revert) {
-        rc = upload_forest(ctx);
-        if (rc != CUPK_OK) return rc;
-    }
     const bool graph = ctx->opts.use_graph != 0 && !ctx->opts.exact;
     const bool direct = !graph && n > kSmallMax && direct_pays(ctx, n);
     // (reverted updates have been classified and accepted: only their scatter)
@@ -1312,14 +1335,18 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert, 
     // (timed contexts time every pass beyond kSmallMax)
     ctx->small_pass = !graph && (n <= kSmallMax ||
                                  (direct && n <= kOneBlockMax && !ctx->opts.time_kernels));
+    uint32_t nd = 0;
+    rc = ctx->small_pass ? delta_forest(ctx, &nd) : revert ? CUPK_OK : upload_forest(ctx);
+    if (rc != CUPK_OK) return rc;
     if (ctx->small_pass) {
         // two launches and one copy: classify into the result block, copy
         // header + flags + positions to the host, scatter with device
         // atomics (the previous small result was read before this pass:
         // every pass waits for its header or for the whole stream)
         uint32_t *derr = &ctx->d_small->hdr[HDR_ERR];
-        HIPCHK(launch_small_classify(ctx->s, d_upd, n, ctx->V, ctx->d_lp, ctx->h_small, derr,
-                                     ctx->d_hdr + HDR_SEQ, ctx->opts.exact != 0));
+        HIPCHK(launch_small_classify(ctx->s, d_upd, n, ctx->V, ctx->d_lp, ctx->h_delta.p, nd,
+                                     ctx->h_small, derr, ctx->d_hdr + HDR_SEQ,
+                                     ctx->opts.exact != 0));
         ctx->hdr_seq++;
         ctx->hdr_word = &ctx->h_small->hdr[HDR_SEQ];
         // the host walks the flags while the scatter runs
@@ -1609,7 +1636,7 @@ static int apply_overlapped(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bo
     // the forest after the walk, for k+1's classification (every earlier
     // reader of the device forest has finished: k's header, which the walk
     // waited for, is published after them)
-    const bool up = ctx->forest_dev_stale;
+    const bool up = upload_due(ctx);
     if (up) {
         rc = upload_forest_on(ctx, ctx->cs);
         if (rc != CUPK_OK) return rc;
@@ -1770,6 +1797,7 @@ void destroy(cupk_ctx *ctx)
     release(ctx->d_items);
     release(ctx->d_bins);
     release(ctx->d_bins1);
+    release(ctx->h_delta);
     release(ctx->d_ccnt);
     release(ctx->d_cgoff);
     release(ctx->d_coff);

@@ -82,7 +82,11 @@ struct cupk_ctx {
     uint64_t *d_lp = nullptr;  // label | parent << 32 per vertex
     uint32_t *d_blk = nullptr; // per 64 vertex ids: their common label, or kBlkMixed
     uint32_t *h_lbl = nullptr, *h_par = nullptr;
-    bool forest_dev_stale = false;
+    bool forest_dev_stale = false;  // lp is older than the host forest
+    // lp is up to date, but the written pages' block labels are not (a small
+    // pass brought only the written vertices' words)
+    bool pages_pending = false;
+    cupk::HostBuf<uint32_t> h_delta;  // (vertex, label, parent) of a small pass
     // page-wise uploads of the forest: the pages written since the last
     // upload, and that list in pinned memory
     std::vector<uint32_t> up_pages;

@@ -566,6 +566,8 @@ class Forest {
     {
         pool_ = p;
         wq_.resize(p ? p->size() : 1);
+        written_.resize(p || !track_ ? 0 : kMaxWritten);
+        n_written_ = written_.size();
     }
     Pool *pool() const { return pool_; }
 
@@ -620,12 +622,27 @@ class Forest {
         pshift_ = shift;
         pages_.assign(((size_t)V_ >> shift) + 1, 1);
         track_ = true;
+        written_.resize(pool_ ? 0 : kMaxWritten);
+        n_written_ = written_.size();
+    }
+    // The vertices whose label or parent was written since the last
+    // take_pages() or take_written(), repeats included; false, with no
+    // effect, when they were more than kMaxWritten (or a pool may have
+    // written some).  The page marks stay.
+    static constexpr size_t kMaxWritten = 1024;
+    bool take_written(std::vector<uint32_t> &out)
+    {
+        if (n_written_ == written_.size()) return false;
+        out.assign(written_.begin(), written_.begin() + n_written_);
+        n_written_ = 0;
+        return true;
     }
     uint32_t page_shift() const { return pshift_; }
     size_t n_pages() const { return pages_.size(); }
     // Append the marked pages to `out` and clear their marks.
     void take_pages(std::vector<uint32_t> &out)
     {
+        n_written_ = 0;
         for (size_t p = 0; p < pages_.size(); p++)
             if (pages_[p]) {
                 out.push_back((uint32_t)p);
@@ -640,10 +657,13 @@ class Forest {
         // stores to the few cache lines of marks from every pool worker
         // would bounce those lines between cores
         if (!track_) return;
+        if (n_written_ < written_.size()) written_[n_written_++] = x;
         uint8_t *m = &pages_[x >> pshift_];
         if (!__atomic_load_n(m, __ATOMIC_RELAXED)) __atomic_store_n(m, (uint8_t)1, __ATOMIC_RELAXED);
     }
     std::vector<uint8_t> pages_;
+    std::vector<uint32_t> written_;  // the first n_written_ count; empty with a pool
+    size_t n_written_ = 0;
     uint32_t pshift_ = 0;
     bool track_ = false;
 

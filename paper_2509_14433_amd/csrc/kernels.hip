@@ -669,15 +669,18 @@ __global__ __launch_bounds__(kDirThreads) void k_scatter_atomic(const BatchDesc 
 // into a result block in coherent pinned host memory, then publishes the next
 // sequence number; a direct scatter follows.  The batch comes in the
 // arguments, so no descriptor copy, header clearing, compaction, binning, copy
-// or event is needed: the latency of a small batch is two launches.
+// or event is needed: the latency of a small batch is two launches.  A few
+// vertices whose forest words changed since the last pass come along (delta):
+// a launch of its own for them made exact mode's chain of passes 7% longer
+// (10,000 updates with 64 cuts: 3.74 instead of 3.49 ms).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kSmallThreads = 1024;
 
 template <uint32_t PT>
 __global__ __launch_bounds__(kSmallThreads) void k_small_classify(
-    const uint64_t *__restrict__ upd, uint32_t n, uint32_t V, const uint64_t *__restrict__ lp,
-    SmallResult *__restrict__ out, uint32_t *__restrict__ derr, uint32_t *__restrict__ seqp,
-    uint32_t with_pos)
+    const uint64_t *__restrict__ upd, uint32_t n, uint32_t V, uint64_t *lp,
+    const uint32_t *__restrict__ delta, uint32_t nd, SmallResult *__restrict__ out,
+    uint32_t *__restrict__ derr, uint32_t *__restrict__ seqp, uint32_t with_pos)
 {
     constexpr uint32_t kWaves = kSmallThreads / 64;
     constexpr uint32_t kCounts = PT * kWaves;  // (step, wave) flag counts
@@ -697,6 +700,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_classify(
     for (uint32_t k = 0; k < PT; k++) {
         const uint32_t i = k * kSmallThreads + threadIdx.x;
         p[k] = i < n ? upd[i] : 0;
+    }
+    if (nd) {  // (repeats of a vertex write the same word)
+        if (threadIdx.x < nd) {
+            const uint32_t *e = delta + 3 * threadIdx.x;
+            const uint32_t w = e[0];
+            if (w < V) lp[w] = (uint64_t)e[1] | (uint64_t)e[2] << 32;
+        }
+        __syncthreads();
     }
     // a few updates' forest words are in flight together
     constexpr uint32_t kGather = 4;
@@ -886,20 +897,20 @@ hipError_t launch_mid_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, De
 }
 
 hipError_t launch_small_classify(hipStream_t s, const uint64_t *upd, uint32_t n, uint32_t V,
-                                 const uint64_t *lp, SmallResult *out, uint32_t *derr,
-                                 uint32_t *seqp, bool with_pos)
+                                 uint64_t *lp, const uint32_t *delta, uint32_t nd,
+                                 SmallResult *out, uint32_t *derr, uint32_t *seqp, bool with_pos)
 {
-    if (n == 0 || n > kOneBlockMax) return hipErrorInvalidValue;
+    if (n == 0 || n > kOneBlockMax || nd > kSmallThreads) return hipErrorInvalidValue;
     const uint32_t wp = with_pos ? 1u : 0u;
     if (n <= kSmallMax)
         k_small_classify<kSmallMax / kSmallThreads>
-            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, out, derr, seqp, wp);
+            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, delta, nd, out, derr, seqp, wp);
     else if (n <= kOneBlockMax / 2)
         k_small_classify<kOneBlockMax / 2 / kSmallThreads>
-            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, out, derr, seqp, wp);
+            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, delta, nd, out, derr, seqp, wp);
     else
         k_small_classify<kOneBlockMax / kSmallThreads>
-            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, out, derr, seqp, wp);
+            <<<1, kSmallThreads, 0, s>>>(upd, n, V, lp, delta, nd, out, derr, seqp, wp);
     return hipGetLastError();
 }
 

@@ -178,14 +178,16 @@ struct SmallResult {
     uint64_t fupd[kOneBlockMax];
     uint32_t fpos[kOneBlockMax];
 };
-// Classify (one block) a batch of 1..kOneBlockMax packed updates given in the
+// First bring the forest words lp of nd (at most 1,024) vertices up to date:
+// (vertex, label, parent) each at `delta` (pinned host memory).  Then
+// classify (one block) a batch of 1..kOneBlockMax packed updates given in the
 // arguments into `out` (coherent pinned host memory; with_pos: also
 // positions), set *derr (device) to the error flag, and publish the next
 // value of the counter *seqp at out->hdr[HDR_SEQ] (release store) once the
 // rest of `out` is written.
 hipError_t launch_small_classify(hipStream_t s, const uint64_t *upd, uint32_t n, uint32_t V,
-                                 const uint64_t *lp, SmallResult *out, uint32_t *derr,
-                                 uint32_t *seqp, bool with_pos);
+                                 uint64_t *lp, const uint32_t *delta, uint32_t nd,
+                                 SmallResult *out, uint32_t *derr, uint32_t *seqp, bool with_pos);
 // Direct scatters, with device atomics, of a classified batch; they do nothing
 // if an update was invalid (*derr set).  Small: at most kSmallMax updates.
 // Mid: any number; a vertex that takes a large share of the batch is gathered
