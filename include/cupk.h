@@ -66,7 +66,15 @@ extern "C" {
 
 /* ---- scatter kernel selection ------------------------------------------ */
 #define CUPK_SCATTER_ATOMIC 0 /* plain kernel: one device atomic XOR per word  */
-#define CUPK_SCATTER_STAGED 1 /* vertex-binned, LDS-staged kernel              */
+#define CUPK_SCATTER_STAGED 1 /* vertex-binned, LDS-staged kernel; batches of
+                                 up to 4,096 updates, and larger ones with few
+                                 (update, column) pairs for the number of
+                                 vertices, go to HBM directly instead.  The
+                                 latter do not when the context sets any of
+                                 tile_vertices, lds_rows, chunk_records,
+                                 tile_grid, fill_reserve, tile_layout or
+                                 coarse_tiles, or replays graphs (which take
+                                 the tiles at any size)                        */
 
 /* ---- staged-scatter lane layouts --------------------------------------- */
 #define CUPK_LAYOUT_RECORD 1  /* one lane per record: up to 24 columns both    */
