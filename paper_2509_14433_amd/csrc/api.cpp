@@ -2001,12 +2001,17 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     // up to 12 as let three blocks share a CU's LDS (every row halves the
     // pairs that go to HBM one by one): 2.0e6 records on 16,384 vertices,
     // C = 14, take 0.033 ms in 16-vertex tiles with 11 rows, 0.035 in
-    // 8-vertex tiles, 0.034 with 8 rows.
+    // 8-vertex tiles, 0.034 with 8 rows.  With eight columns and fewer a tile
+    // of 16 vertices is too little work for a block, so it grows to 256
+    // (vertex, column) pairs: 200,000 updates at V = 2^20, us a batch, 16
+    // vertices / more: C = 1 (256 vertices) 210 / 119, C = 2 (128) 213 / 127,
+    // C = 4 (64) 215 / 143, C = 8 (32) 286 / 222; 6e6 at C = 8: 601 / 603.
     uint32_t rows = ctx->opts.lds_rows ? ctx->opts.lds_rows : 8;
     rows = std::min(rows, D);
     uint32_t tv = ctx->opts.tile_vertices;
     if (tv == 0 && C <= kStagMaxC) {
         tv = V >= 16 * 768 ? 16 : V >= 8 * 768 ? 8 : 4;
+        while (2 * tv * C <= 256 && V >= 2 * tv * 768) tv *= 2;
         auto fits = [&](uint32_t r, uint32_t t) {
             return tile_geometry_fits(r, C, t, kLayoutPair) &&
                    ((size_t)(r + 1) * t + 1) * C * 16 <= 53248;

@@ -1,0 +1,72 @@
+"""The default route and geometry against the one a caller can name instead:
+where the two differ, the default may not be the slower one by more than the
+noise.  Times are the least of several runs of the same batches on one GPU,
+and what each case guards against was slower by half or more."""
+import time
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def cupk():
+    import torch
+    assert torch.cuda.is_available(), "GPU test on a machine without a GPU"
+    import paper_2509_14433_amd as m
+    return m
+
+
+def _batch(V, n, hub=0.0, seed=1):
+    """n updates between random vertices, a share `hub` of them at vertex 7."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.randint(V, (n,), generator=g, device="cuda")
+    v = (u + 1 + torch.randint(V - 1, (n,), generator=g, device="cuda")) % V
+    if hub:
+        u = torch.where(torch.rand(n, generator=g, device="cuda") < hub, 7, u)
+        v = torch.where(u == v, (v + 1) % V, v)
+    return torch.minimum(u, v) | (torch.maximum(u, v) << 32)
+
+
+def _tree(ctx, V):
+    """One tree over all vertices: later inserts flag nothing."""
+    import torch
+    w = torch.arange(1, V, device="cuda")
+    for s in range(0, V - 1, 1 << 20):
+        x = w[s:s + (1 << 20)]
+        ctx.apply_updates_device((x // 2) | (x << 32))
+    ctx.sync()
+
+
+def _us(ctx, p, reps=10, tries=5):
+    best = float("inf")
+    for _ in range(tries):
+        ctx.sync()
+        t = time.perf_counter()
+        for _ in range(reps):
+            ctx.apply_updates_device(p)
+        ctx.sync()
+        best = min(best, (time.perf_counter() - t) / reps)
+    return best * 1e6
+
+
+def _pair(cupk, V, C, p, one, other, D=0):
+    """us a batch of p in contexts with options `one` and `other`."""
+    got = []
+    for kw in (one, other):
+        ctx = cupk.Context(V, C, D, seed=1, **kw)
+        _tree(ctx, V)
+        _us(ctx, p, tries=1)
+        got.append(_us(ctx, p))
+        ctx.close()
+    print(f"V={V} C={C} n={p.numel()} {one} {got[0]:.1f} us, {other} {got[1]:.1f} us", flush=True)
+    return got
+
+
+@pytest.mark.parametrize("C,tv", [(1, 256), (4, 64)])
+def test_few_columns_get_larger_tiles(cupk, C, tv):
+    V = 1 << 20
+    auto, named = _pair(cupk, V, C, _batch(V, 200_000), dict(chunk_records=4096),
+                        dict(chunk_records=4096, tile_vertices=tv))
+    assert auto < 1.25 * named
