@@ -1286,16 +1286,24 @@ static int enqueue_split_back(cupk_ctx *ctx, uint32_t n)
 
 // Whether a batch of n > kSmallMax updates goes to HBM directly (one device
 // atomic per changed word) instead of through the tiles.  The direct pass
-// costs about 14 us and 52 ps per (update, column); the staged one a chain of
-// short kernels and the lines of the touched vertices, which grow with V
-// (classification included, us, direct / staged): V = 16,384: 22 / 33 at
-// 10,000 updates, 44 / 37 at 40,000; 65,536: 31 / 71 at 20,000, 76 / 78 at
-// 80,000; 131,072: 85 / 100 at 80,000, 156 / 125 at 160,000; 2^20: 94 / 308
-// at 80,000.  Uniform batches break even near 380K, 1.3M and 1.8M pairs (at
-// V = 1,024 near 170K).  The line is drawn lower because updates that share a
-// vertex serialize on its words (17 ns each; k_mid_scatter takes the edge off):
-// with one vertex in a tenth of 8,000 updates on 16,384 vertices both take
-// 33 us.  A caller that sets the tile geometry gets the tiles.
+// costs about 14 us and 52 ps per (update, column), and 1.1 ns more per update
+// when one vertex takes 5 to 35% of them: updates that share a vertex
+// serialize on its words (17 ns each), and k_mid_scatter gathers it only in
+// the blocks that have it among their first few endpoints.  The staged pass
+// costs a chain of short kernels and the lines of the touched vertices, which
+// grow with V and C.  The line is drawn where the worst of uniform batches,
+// R-MAT batches and batches with one or four such vertices costs about the
+// same on both ways, in units of 52 ps: 13 us of chain and C min(V/2, 32768 +
+// V/4) for the lines.  The worst ratio of direct to staged below and above the
+// line (n at it): V = 1,024, C = 10 (8,200): 8,000 updates 0.97, 10,000 1.2;
+// 16,384, C = 14 (9,362): 8,000 0.94; 65,536, C = 4 (15,200): 16,000 1.08,
+// 32,000 1.3; 65,536, C = 16 (20,900): 23,000 0.94, 32,000 1.13; 131,072, C =
+// 17 (35,800): 32,000 0.94, 45,000 1.16, 61,680 1.45; 2^20, C = 1 (24,700):
+// 23,000 0.3, 180,000 1.09; 2^20, C = 4 (57,200): 64,000 0.63, 128,000 1.13;
+// 2^20, C = 20 (150,000): 128,000 0.92, 180,000 1.12, 420,000 2.1 (uniform
+// batches there: 0.41, 0.51, 1.04).  The second bound is as far as
+// direct batches have been measured.  A caller that sets the tile geometry
+// gets the tiles.
 static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
 {
     if (ctx->opts.scatter_mode != CUPK_SCATTER_STAGED) return true;
@@ -1303,7 +1311,9 @@ static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
     if (o.tile_vertices || o.lds_rows || o.chunk_records || o.tile_grid || o.fill_reserve ||
         o.tile_layout || o.coarse_tiles)
         return false;
-    return (uint64_t)n * ctx->C <= std::max<uint64_t>(100000, 8 * (uint64_t)ctx->V);
+    const uint64_t V = ctx->V, C = ctx->C;
+    return n * (C + 21) <= 250000 + C * std::min(V / 2, 32768 + V / 4) &&
+           n * C <= std::max<uint64_t>(100000, 8 * V);
 }
 
 // The scatter of n updates that a small pass classified, or that a pass

@@ -70,3 +70,16 @@ def test_few_columns_get_larger_tiles(cupk, C, tv):
     auto, named = _pair(cupk, V, C, _batch(V, 200_000), dict(chunk_records=4096),
                         dict(chunk_records=4096, tile_vertices=tv))
     assert auto < 1.25 * named
+
+
+@pytest.mark.parametrize("V,C,n,hub", [
+    (131072, 0, 60_000, 0.2), (1 << 20, 0, 400_000, 0.2), (1 << 20, 4, 1_000_000, 0.1),
+    (65536, 1, 360_000, 0.1), (1024, 4, 24_000, 0.2)])
+def test_direct_scatter_ends_where_tiles_win_with_a_hub(cupk, V, C, n, hub):
+    auto, tiles = _pair(cupk, V, C, _batch(V, n, hub), {}, dict(chunk_records=4096))
+    assert auto < 1.25 * tiles
+
+
+def test_small_batches_of_a_large_graph_stay_direct(cupk):
+    auto, tiles = _pair(cupk, 1 << 20, 0, _batch(1 << 20, 50_000), {}, dict(chunk_records=4096))
+    assert auto < 0.7 * tiles

@@ -1,4 +1,5 @@
-"""Exact and levels mode on every scatter route, against the oracle.
+"""Scatter routes against the oracle: exact and levels mode on each, and batches
+around the sizes where a route ends.
 
 By default a staged context sends a batch of a few thousand updates to HBM
 directly; naming a lane layout sends it through the tiles.  Exact mode then
@@ -90,4 +91,37 @@ def test_levels_mode_on_every_route(cupk, route):
     assert ctx.digest() == sk.digest()
     ctr = ctx.counters()
     assert (ctr["links"], ctr["cuts"]) == (fr.n_links, fr.n_cuts)
+    ctx.close()
+
+
+@pytest.mark.parametrize("hub", [False, True])
+@pytest.mark.parametrize("V,C,n", [
+    # one block classifies up to 16,384 updates
+    (65536, 16, 16384), (65536, 16, 16385),
+    # the direct scatter ends: n * (C + 21) against 250,000 + C * V / 2
+    (65536, 16, 20926), (65536, 16, 20927),
+    # n * C against 100,000
+    (3001, 20, 5000), (3001, 20, 5001)])
+def test_batches_where_routes_meet(cupk, V, C, n, hub):
+    S, D = 0x10AD + n, 12
+    rng = np.random.default_rng(n)
+    k = np.unique(rng.integers(0, V, (2 * n, 2)), axis=0)
+    if hub:
+        k[: len(k) // 4, 0] = 11
+        k = np.unique(k, axis=0)
+    k = k[k[:, 0] != k[:, 1]]
+    # one direction of each pair
+    key = np.minimum(k[:, 0], k[:, 1]) * V + np.maximum(k[:, 0], k[:, 1])
+    k = k[np.unique(key, return_index=True)[1]]
+    k = k[rng.permutation(len(k))[:n]].astype(np.uint32)
+    assert len(k) == n
+    u, v = k[:, 0].copy(), k[:, 1].copy()
+    print(f"routes V={V} C={C} n={n} hub={hub}", flush=True)
+    ctx = cupk.Context(V, C, D, S)
+    ref = oracle.Sketch(V, C, D, S)
+    ctx.apply_updates(u, v, np.zeros(n, np.uint8))
+    ref.apply(u, v)
+    a, g = ctx.get_sketch()
+    assert np.array_equal(a, ref.alpha) and np.array_equal(g, ref.gamma)
+    assert ctx.num_components() == oracle.uf_components(V, u, v)[0]
     ctx.close()
