@@ -1713,10 +1713,11 @@ DEVI void tile_pair(uint8_t *lds8, uint32_t RSB, uint32_t pg, uint32_t rows, uin
     }
 }
 
-// More than kStagMaxC columns, more than 31 rows, or wide records.  One (record, column)
-// pair per lane: the edge index x = u*V + v of the record's update is hashed
-// for column c and (x, h) is XOR-ed into bucket (d, c) of its endpoint.  Lane l of a wave takes column l mod C of
-// record l / C (G = 64 / C records per wave step, lanes l >= G*C idle), so
+// More than kStagMaxC columns, or wide records.  One (record, column) pair per
+// lane: the edge index x = u*V + v of the record's update is hashed for column
+// c and (x, h) is XOR-ed into bucket (d, c) of its endpoint.  Lane l of a wave
+// takes column l mod C of record l / C (G = 64 / C records per wave step,
+// lanes l >= G*C idle), so
 // the C lanes of a record hit C consecutive LDS words and the hash seed is a
 // per-lane constant.
 //
@@ -1885,9 +1886,13 @@ hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const S
     const size_t delta = (size_t)2 * p.rows * sk.C * (1u << p.tile_shift) * sizeof(uint64_t);
     if (!tile_geometry_fits(p.rows, sk.C, 1u << p.tile_shift, p.layout))
         return hipErrorInvalidValue;
-    const uint32_t rfast = min(p.rows, sk.D - 1);
     const bool wide = rec_wide(sk.V, p.tile_shift);
-    if (sk.C <= kStagMaxC && rfast <= 31 && !wide) {
+    if (sk.C <= kStagMaxC && !wide) {
+        // (rows beyond what one word's trailing zero count tells would hold a
+        // pair in 2^31: it goes to HBM like any deep one, 167 us against 326
+        // in the pair kernel with 36 rows, 1,000,000 updates on 65,536
+        // vertices, C = 20)
+        const uint32_t rows = min(p.rows, 31u), rfast = min(rows, sk.D - 1);
         const size_t lds = ((size_t)(rfast + 1) * sk.C * 16 << p.tile_shift) + (size_t)sk.C * 16;
         if (lds > kCuLds) return hipErrorInvalidValue;
         // Dense batches (64 records per vertex and more) have heavy items:
@@ -1905,7 +1910,7 @@ hipError_t launch_tile(hipStream_t s, DevSketch sk, const uint32_t *hdr, const S
             constexpr uint32_t C = decltype(cc)::value + 1;
             if (sk.C != C) return;
             k_tile_scatter_stag<C><<<grid, kStagThreads, lds, s>>>(
-                sk, bins, tile_off, items, nitems, p.tile_shift, p.rows, p.chunk, hdr, touched);
+                sk, bins, tile_off, items, nitems, p.tile_shift, rows, p.chunk, hdr, touched);
             e = hipGetLastError();
         };
         for_columns(go);

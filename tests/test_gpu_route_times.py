@@ -72,6 +72,13 @@ def test_few_columns_get_larger_tiles(cupk, C, tv):
     assert auto < 1.25 * named
 
 
+def test_many_lds_rows_keep_the_kernel(cupk):
+    V = 65536
+    many, few = _pair(cupk, V, 20, _batch(V, 1_000_000), dict(lds_rows=36, tile_vertices=4),
+                      dict(lds_rows=31, tile_vertices=4), D=40)
+    assert many < 1.1 * few
+
+
 @pytest.mark.parametrize("V,C,n,hub", [
     (131072, 0, 60_000, 0.2), (1 << 20, 0, 400_000, 0.2), (1 << 20, 4, 1_000_000, 0.1),
     (65536, 1, 360_000, 0.1), (1024, 4, 24_000, 0.2)])
