@@ -443,9 +443,11 @@ int cupk_static_components(cupk_ctx *ctx, uint32_t *labels, uint32_t *eu, uint32
  * candidate's device work (classification, tile scan, binning, scatter) on
  * a sample batch and timing the best four again (two alternating passes,
  * which decide), then the tiles per coarse bin of the two-level binning for
- * that setting; and derives a batch-size schedule: the device time of prefixes n/128 .. n of
- * the sample plus the host time per batch this context has measured so far
- * (flag walk and replacement rounds, nearly independent of the batch size);
+ * that setting; and derives a batch-size schedule: the device time of prefixes
+ * n/128 .. n of the sample, each on the route that a batch of that size takes
+ * (CUPK_SCATTER_STAGED), plus the host time per batch this context has
+ * measured so far (flag walk and replacement rounds, nearly independent of the
+ * batch size);
  * batch_target is the smallest prefix whose whole-path rate reaches 80% of
  * the best one.  The serving loop then uses batch_target as its batch size
  * unless cupk_serve_opts.max_batch is set.  Each candidate applies the

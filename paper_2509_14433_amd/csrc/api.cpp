@@ -1316,6 +1316,13 @@ static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
            n * C <= std::max<uint64_t>(100000, 8 * V);
 }
 
+// Whether one block classifies a batch of n updates that is not binned.
+// (Timed contexts time every pass beyond kSmallMax.)
+static bool one_block(const cupk_ctx *ctx, uint32_t n)
+{
+    return n <= kSmallMax || (n <= kOneBlockMax && !ctx->opts.time_kernels);
+}
+
 // The scatter of n updates that a small pass classified, or that a pass
 // before it did (derr: a word that stays zero).
 static int enqueue_small_scatter(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n,
@@ -1342,9 +1349,7 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert, 
     // (reverted updates have been classified and accepted: only their scatter)
     if (revert && (n <= kSmallMax || direct))
         return enqueue_small_scatter(ctx, d_upd, n, small_zero(ctx));
-    // (timed contexts time every pass beyond kSmallMax)
-    ctx->small_pass = !graph && (n <= kSmallMax ||
-                                 (direct && n <= kOneBlockMax && !ctx->opts.time_kernels));
+    ctx->small_pass = !graph && (n <= kSmallMax || direct) && one_block(ctx, n);
     uint32_t nd = 0;
     rc = ctx->small_pass ? delta_forest(ctx, &nd) : revert ? CUPK_OK : upload_forest(ctx);
     if (rc != CUPK_OK) return rc;
@@ -2459,38 +2464,57 @@ int cupk_sync(cupk_ctx *ctx)
     });
 }
 
-// Time the bin + scatter of `n` sample updates (one application) with the
-// geometry in force, reading the tile counts from a classify pass.
-static int time_scatter_once(cupk_ctx *ctx, const uint64_t *d, uint32_t n, hipEvent_t e0,
-                             hipEvent_t e1, float *ms)
+// Time the device work of `n` sample updates (one application): through the
+// tiles with the geometry in force, or, with any_route, on the route that a
+// batch of n updates takes in this context (enqueue_pass).
+static int time_scatter_once(cupk_ctx *ctx, const uint64_t *d, uint32_t n, bool any_route,
+                             hipEvent_t e0, hipEvent_t e1, float *ms)
 {
     int rc = ensure_batch_buffers(ctx, n);
     if (rc != CUPK_OK) return rc;
+    const bool graph = ctx->opts.use_graph != 0 && !ctx->opts.exact;
+    const bool direct = any_route && !graph && (n <= kSmallMax || direct_pays(ctx, n));
+    const bool small = direct && one_block(ctx, n);
     ctx->cur_desc.upd = d;
     ctx->cur_desc.n = n;
     HIPCHK(hipEventRecord(e0, ctx->s));
-    rc = enqueue_classify(ctx, ctx->s, n);
-    ctx->hdr_seq++;  // published by the scan kernel (read after the sync below)
+    const uint32_t *derr = ctx->d_hdr + HDR_REJ;
+    if (small) {
+        uint32_t *word = &ctx->d_small->hdr[HDR_ERR];
+        HIPCHK(launch_small_classify(ctx->s, d, n, ctx->V, ctx->d_lp, nullptr, 0, ctx->h_small,
+                                     word, ctx->d_hdr + HDR_SEQ, ctx->opts.exact != 0));
+        derr = word;
+    } else {
+        rc = enqueue_classify(ctx, ctx->s, n, false, direct);
+    }
+    ctx->hdr_seq++;  // published by the kernel above (read after the sync below)
     if (rc != CUPK_OK) return rc;
-    rc = enqueue_bin(ctx, ctx->s, n);
-    if (rc == CUPK_OK) rc = enqueue_tile(ctx, ctx->s, n, false);
-    if (rc != CUPK_OK) return rc;
+    if (direct) {
+        HIPCHK(n <= kSmallMax
+                   ? launch_small_scatter(ctx->s, d, n, dev_sketch(ctx), derr)
+                   : launch_mid_scatter(ctx->s, d, n, dev_sketch(ctx), derr, nullptr));
+    } else {
+        rc = enqueue_bin(ctx, ctx->s, n);
+        if (rc == CUPK_OK) rc = enqueue_tile(ctx, ctx->s, n, false);
+        if (rc != CUPK_OK) return rc;
+    }
     HIPCHK(hipEventRecord(e1, ctx->s));
     HIPCHK(hipEventSynchronize(e1));
     HIPCHK(hipEventElapsedTime(ms, e0, e1));
-    if (ctx->h_hdr[HDR_ERR]) return ctx->invalid("sample batch holds an invalid update");
+    if ((small ? ctx->h_small->hdr : ctx->h_hdr)[HDR_ERR])
+        return ctx->invalid("sample batch holds an invalid update");
     return CUPK_OK;
 }
 
 // Median over `reps` pairs of applications (each pair cancels out).
 static int time_scatter(cupk_ctx *ctx, const uint64_t *d, uint32_t n, int reps, hipEvent_t e0,
-                        hipEvent_t e1, double *out_ms)
+                        hipEvent_t e1, double *out_ms, bool any_route = false)
 {
     std::vector<float> t;
     for (int r = 0; r < reps; r++)
         for (int k = 0; k < 2; k++) {
             float ms = 0;
-            int rc = time_scatter_once(ctx, d, n, e0, e1, &ms);
+            int rc = time_scatter_once(ctx, d, n, any_route, e0, e1, &ms);
             if (rc != CUPK_OK) return rc;
             t.push_back(ms);
         }
@@ -2773,7 +2797,8 @@ int cupk_autotune(cupk_ctx *ctx, const uint64_t *d_sample, size_t n, cupk_tune_r
             best = std::min(best, best_co);
             if (rc == CUPK_OK) rc = set_geometry(ctx, btv, brows, bchunk, blay, bco);
         }
-        // batch-size schedule: device time of prefixes n/128 .. n, plus the
+        // batch-size schedule: device time of prefixes n/128 .. n, each on
+        // the route that a batch of its size takes, plus the
         // host time per batch (flag walk and replacement rounds, which cost
         // about the same whatever the batch size) measured on this
         // context's batches so far; the target is the smallest prefix whose
@@ -2787,7 +2812,7 @@ int cupk_autotune(cupk_ctx *ctx, const uint64_t *d_sample, size_t n, cupk_tune_r
         for (int k = 0; k < 8 && rc == CUPK_OK; k++) {
             const uint32_t sz = std::max<uint32_t>(1, m >> (7 - k));
             double ms = 0;
-            rc = time_scatter(ctx, d_sample, sz, 2, e0, e1, &ms);
+            rc = time_scatter(ctx, d_sample, sz, 2, e0, e1, &ms, true);
             out->batch_sizes[k] = sz;
             out->batch_ms[k] = ms;
             if (ms + host_ms > 0) best_rate = std::max(best_rate, sz / (ms + host_ms));

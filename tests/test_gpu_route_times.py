@@ -90,3 +90,23 @@ def test_direct_scatter_ends_where_tiles_win_with_a_hub(cupk, V, C, n, hub):
 def test_small_batches_of_a_large_graph_stay_direct(cupk):
     auto, tiles = _pair(cupk, 1 << 20, 0, _batch(1 << 20, 50_000), {}, dict(chunk_records=4096))
     assert auto < 0.7 * tiles
+
+
+def test_autotuner_schedule_times_the_route_a_batch_takes(cupk):
+    V, C = 1 << 20, 8
+    sample = _batch(V, 1 << 20)
+    got = []
+    for kw in ({}, dict(chunk_records=4096)):
+        ctx = cupk.Context(V, C, 16, seed=1, **kw)
+        before = ctx.digest()
+        r = ctx.autotune(sample)
+        assert ctx.digest() == before and r["batch_sizes"][0] == 8192
+        got.append(r["batch_ms"])
+        _tree(ctx, V)
+        got[-1].append(_us(ctx, sample[:8192]) / 1e3)
+        ctx.close()
+    print("schedule ms", got, flush=True)
+    # 8,192 updates of a million vertices go to HBM directly unless a geometry is named
+    assert got[0][0] < 0.6 * got[1][0]
+    for ms in got:
+        assert ms[0] < 1.5 * ms[8] + 0.02
