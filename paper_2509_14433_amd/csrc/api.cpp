@@ -1976,8 +1976,10 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     HIPCHK(hipMalloc((void **)&ctx->d_par, (size_t)V * 4));
     HIPCHK(hipMalloc((void **)&ctx->d_lp, (size_t)V * 8));
     HIPCHK(hipMalloc((void **)&ctx->d_blk, (((size_t)V + 63) >> kBlkShift) * 4));
-    HIPCHK(hipHostMalloc((void **)&ctx->h_lbl, (size_t)V * 4, hipHostMallocDefault));
-    HIPCHK(hipHostMalloc((void **)&ctx->h_par, (size_t)V * 4, hipHostMallocDefault));
+    // coherent: k_load_forest reads both in place while the host rewrites them
+    // between passes
+    HIPCHK(hipHostMalloc((void **)&ctx->h_lbl, (size_t)V * 4, hipHostMallocCoherent));
+    HIPCHK(hipHostMalloc((void **)&ctx->h_par, (size_t)V * 4, hipHostMallocCoherent));
     HIPCHK(hipMalloc((void **)&ctx->d_hdr, HDR_WORDS * 4));
     HIPCHK(hipMemset(ctx->d_hdr, 0, HDR_WORDS * 4));
     // coherent: the scan kernel's stores reach the host without a flush
