@@ -131,12 +131,14 @@ typedef struct {
      * whole; at the first update that cuts a forest edge, the scatter of
      * the updates after it is undone (applied again: XOR toggles back), the
      * cut and its replacement rounds run on the sketch as of that update,
-     * and the rest of the batch is processed again the same way.  The
-     * forest then equals the one obtained by applying the updates one at a
-     * time (batches of one), whatever the batch size, as long as no
-     * replacement query fails (a failed tree is retried at the next cut or
-     * batch end rather than after every update).  Captured graphs
-     * (use_graph) are not used in this mode. */
+     * and the rest of the batch is processed again the same way, except
+     * that passes classified by one block are from then on scattered only
+     * up to their cut, which leaves nothing to undo.  The forest then equals
+     * the one obtained by applying the updates one at a time (batches of
+     * one), whatever the batch size, as long as no replacement query fails
+     * (a failed tree is retried at the next cut or batch end rather than
+     * after every update).  Captured graphs (use_graph) are not used in this
+     * mode. */
     uint32_t exact;
     /* Nonzero: multi-level hierarchy (Gibb's cutset levels, Sec. 2.2.2 and
      * Alg. 1).  Levels 0..C: level i < C keeps its own forest and queries
@@ -178,7 +180,9 @@ typedef struct {
     /* Lane layout of the staged scatter: CUPK_LAYOUT_RECORD, CUPK_LAYOUT_PAIR
      * or 0.  The kernel follows from the number of columns (see the
      * constants), so this only decides which tile geometries are accepted:
-     * RECORD admits a delta of 64 KiB, PAIR one of 52 KiB. */
+     * RECORD admits a delta of 64 KiB, PAIR one of 52 KiB; 0 is PAIR when
+     * max_batch is at least 4,194,304, else RECORD.  Naming one also keeps
+     * batches off the direct scatter (CUPK_SCATTER_STAGED). */
     uint32_t tile_layout;
     /* Nonzero: finish each batch's replacement rounds before the next batch
      * is classified.  Default: when a device batch follows one whose host
@@ -241,10 +245,12 @@ typedef struct {
                                     without a sketch                            */
     uint64_t sets_complemented;  /* trees holding such a piece reduced from the
                                     other pieces (all pieces XOR to zero)       */
-    uint64_t timed_buckets;      /* buckets the timed staged scatter launches
-                                    changed in HBM (nonzero folded delta, or a
-                                    record's deep-row bucket): 32 B of
-                                    compulsory traffic each (read + write)      */
+    uint64_t timed_buckets;      /* buckets the timed launches of a staged
+                                    context changed in HBM (nonzero folded
+                                    delta, or a bucket that a record or a block
+                                    of the direct scatter changes by atomics):
+                                    32 B of compulsory traffic each (read +
+                                    write)                                      */
     uint64_t overlapped;         /* batches classified and binned while the
                                     previous batch's rounds ran                 */
 } cupk_counters_t;
