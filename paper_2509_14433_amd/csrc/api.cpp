@@ -2021,15 +2021,18 @@ int init_impl(cupk_ctx *ctx, const cupk_opts *opts)
     // C = 14, take 0.033 ms in 16-vertex tiles with 11 rows, 0.035 in
     // 8-vertex tiles, 0.034 with 8 rows.  With eight columns and fewer a tile
     // of 16 vertices is too little work for a block, so it grows to 256
-    // (vertex, column) pairs: 200,000 updates at V = 2^20, us a batch, 16
-    // vertices / more: C = 1 (256 vertices) 210 / 119, C = 2 (128) 213 / 127,
-    // C = 4 (64) 215 / 143, C = 8 (32) 286 / 222; 6e6 at C = 8: 601 / 603.
+    // (vertex, column) pairs, as long as its records take 32 bits: 200,000
+    // updates at V = 2^20, us a batch, 16 vertices / more: C = 1 (256
+    // vertices) 210 / 119, C = 2 (128) 213 / 127, C = 4 (64) 215 / 143, C = 8
+    // (32) 286 / 222; 6e6 at C = 8: 601 / 603.
     uint32_t rows = ctx->opts.lds_rows ? ctx->opts.lds_rows : 8;
     rows = std::min(rows, D);
     uint32_t tv = ctx->opts.tile_vertices;
     if (tv == 0 && C <= kStagMaxC) {
         tv = V >= 16 * 768 ? 16 : V >= 8 * 768 ? 8 : 4;
-        while (2 * tv * C <= 256 && V >= 2 * tv * 768) tv *= 2;
+        while (2 * tv * C <= 256 && V / (2 * tv) >= 768 &&
+               !rec_wide(V, (uint32_t)__builtin_ctz(2 * tv)))
+            tv *= 2;
         auto fits = [&](uint32_t r, uint32_t t) {
             return tile_geometry_fits(r, C, t, kLayoutPair) &&
                    ((size_t)(r + 1) * t + 1) * C * 16 <= 53248;
