@@ -1287,24 +1287,21 @@ static int enqueue_split_back(cupk_ctx *ctx, uint32_t n)
 
 // Whether a batch of n > kSmallMax updates goes to HBM directly (one device
 // atomic per changed word) instead of through the tiles.  The direct pass
-// costs about 14 us and 52 ps per (update, column), and 1.1 ns more per update
-// when one vertex takes 5 to 35% of them: updates that share a vertex
-// serialize on its words (17 ns each), and k_mid_scatter gathers it only in
-// the blocks that have it among their first few endpoints.  The staged pass
-// costs a chain of short kernels and the lines of the touched vertices, which
-// grow with V and C.  The line is drawn where the worst of uniform batches,
-// R-MAT batches and batches with one or four such vertices costs about the
-// same on both ways, in units of 52 ps: 13 us of chain and C min(V/2, 32768 +
-// V/4) for the lines.  The worst ratio of direct to staged below and above the
-// line (n at it): V = 1,024, C = 10 (8,200): 8,000 updates 0.97, 10,000 1.2;
-// 16,384, C = 14 (9,362): 8,000 0.94; 65,536, C = 4 (15,200): 16,000 1.08,
-// 32,000 1.3; 65,536, C = 16 (20,900): 23,000 0.94, 32,000 1.13; 131,072, C =
-// 17 (35,800): 32,000 0.94, 45,000 1.16, 61,680 1.45; 2^20, C = 1 (24,700):
-// 23,000 0.3, 180,000 1.09; 2^20, C = 4 (57,200): 64,000 0.63, 128,000 1.13;
-// 2^20, C = 20 (150,000): 128,000 0.92, 180,000 1.12, 420,000 2.1 (uniform
-// batches there: 0.41, 0.51, 1.04).  The second bound is as far as
-// direct batches have been measured.  A caller that sets the tile geometry
-// gets the tiles.
+// costs about 14 us and 52 ps per (update, column), and up to 60% more when a
+// few vertices take 5 to 40% of the updates or degrees follow a power law; the
+// staged pass a chain of short kernels and the lines of the touched vertices,
+// which grow with V and C.  The line is drawn where the worst of uniform
+// batches, R-MAT batches and batches with one or four such vertices costs
+// about the same on both ways.  That worst ratio of direct to staged below and
+// above the line (n at it): V = 1,024, C = 1 (50,600): 45,000 updates 0.94,
+// 64,000 1.09; 1,024, C = 10 (9,400): 8,000 0.80, 11,000 0.93; 16,384, C = 14
+// (11,600): 11,000 0.94, 16,000 1.14; 65,536, C = 4 (46,200): 45,000 1.07;
+// 65,536, C = 16 (25,100): 23,000 0.94, 32,000 1.11; 131,072, C = 17 (43,800):
+// 45,000 0.86, 64,000 1.03; 2^20, C = 4 (308,000): 256,000 0.7, 360,000 0.92,
+// 512,000 1.16; 2^20, C = 20 (149,000): 128,000 0.90, 180,000 1.06, 256,000
+// 1.24 (uniform batches there: 0.41, 0.51, 0.71); 2^22, C = 8 (651,000):
+// 720,000 0.90, 1,000,000 1.08.  A caller that sets the tile geometry gets the
+// tiles.
 static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
 {
     if (ctx->opts.scatter_mode != CUPK_SCATTER_STAGED) return true;
@@ -1313,8 +1310,7 @@ static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
         o.tile_layout || o.coarse_tiles)
         return false;
     const uint64_t V = ctx->V, C = ctx->C;
-    return n * (C + 21) <= 250000 + C * std::min(V / 2, 32768 + V / 4) &&
-           n * C <= std::max<uint64_t>(100000, 8 * V);
+    return n * (C + 1) <= 100000 + V + C * std::min(V / 4, 65536 + V / 32);
 }
 
 // Whether one block classifies a batch of n updates that is not binned.

@@ -822,34 +822,80 @@ DEVI void add_touched(unsigned long long *touched, uint32_t t, uint32_t *sum)
     }
 }
 
-// Direct scatter of medium batches: as scatter_direct, but a block takes
-// kMidPer updates, and the changes to eight vertices, the endpoints of four
-// of them, are gathered in LDS (rows below kMidRows) and sent once.  A vertex that takes a large share of a batch is among them
-// in most blocks; one atomic per update on its words would serialize at about
-// 17 ns each (a star of 16,000 updates: 293 us instead of 37).
-constexpr uint32_t kMidPer = 32;
+// Direct scatter of medium batches: as scatter_direct, but a block takes `per`
+// updates (a power of two up to kMidMax), counts their endpoints in an LDS
+// hash table, and gathers the changes to up to eight vertices that many of
+// them share in LDS (rows below kMidRows), sent once.  Bound by the requests of
+// device-scope atomics; one per update on the words of a vertex that takes a
+// large share of a batch would serialize at about 17 ns each.  131,072 updates
+// at V = 131,072, C = 4, a tenth of them at one vertex: 58 us, 139 when only
+// the endpoints of four updates in 32 were looked at; uniform ones 42 and 41.
+constexpr uint32_t kMidMax = kDirThreads;  // one update per thread when counting
 constexpr uint32_t kMidRows = 8;
 constexpr uint32_t kMidVerts = 8;
+constexpr uint32_t kMidTable = 4 * kMidMax;  // hash entries: at most half are used
 
 __global__ __launch_bounds__(kDirThreads) void k_mid_scatter(const uint64_t *__restrict__ upd,
                                                              uint32_t n, DevSketch sk,
                                                              const uint32_t *__restrict__ derr,
+                                                             uint32_t per,
                                                              unsigned long long *__restrict__ touched)
 {
     extern __shared__ uint64_t lds[];  // [vertex][row][column][alpha, gamma]
+    __shared__ uint32_t key[kMidTable], cnt[kMidTable];
+    __shared__ uint32_t hot[kMidVerts], nhot;
+    __shared__ uint8_t slot[2 * kMidMax];
     if (*derr) return;
     const uint32_t C = sk.C;
-    const uint32_t row = 2 * C, per_v = kMidRows * row;
-    const uint32_t begin = blockIdx.x * kMidPer, end = min(n, begin + kMidPer);
-    for (uint32_t q = threadIdx.x; q < kMidVerts * per_v; q += kDirThreads) lds[q] = 0;
-    uint32_t hot[kMidVerts];
-    {
-        bool del;
-#pragma unroll
-        for (uint32_t t = 0; t < kMidVerts / 2; t++)
-            unpack(upd[begin + (end - begin) * t / (kMidVerts / 2)], sk.V, hot[2 * t],
-                   hot[2 * t + 1], del);
+    const uint32_t per_v = kMidRows * 2 * C;
+    const uint32_t begin = blockIdx.x * per, m = min(n - begin, per);
+    const uint32_t tab = 4 * per;
+    for (uint32_t t = threadIdx.x; t < tab; t += kDirThreads) {
+        key[t] = 0xffffffffu;  // no vertex (V <= 2^31)
+        cnt[t] = 0;
     }
+    if (threadIdx.x == 0) nhot = 0;
+    uint32_t e[2] = {0, 0}, at[2] = {0, 0};
+    bool del;
+    if (threadIdx.x < m) unpack(upd[begin + threadIdx.x], sk.V, e[0], e[1], del);
+    __syncthreads();
+    if (threadIdx.x < m) {
+        const uint32_t shift = (uint32_t)__builtin_clz(tab) + 1;  // 32 - log2(tab)
+#pragma unroll
+        for (uint32_t k = 0; k < 2; k++) {
+            uint32_t h = (e[k] * 0x9E3779B1u) >> shift;
+            for (;; h = (h + 1) & (tab - 1)) {
+                const uint32_t old = atomicCAS(&key[h], 0xffffffffu, e[k]);
+                if (old == 0xffffffffu || old == e[k]) break;
+            }
+            at[k] = h;
+            atomicAdd(&cnt[h], 1u);
+        }
+    }
+    // places for the vertices with the most updates: first those with a
+    // sixteenth of the block's or more, then any with three
+    constexpr uint32_t kPlaced = 1u << 31;
+    for (uint32_t many = max(per / 16, 4u); many; many = many > 3 ? 3 : 0) {
+        __syncthreads();
+        for (uint32_t t = threadIdx.x; t < tab; t += kDirThreads) {
+            const uint32_t c = cnt[t];
+            if (c < many || c >= kPlaced) continue;
+            const uint32_t p = atomicAdd(&nhot, 1u);
+            if (p >= kMidVerts) continue;
+            hot[p] = key[t];
+            cnt[t] = kPlaced | p;
+        }
+    }
+    __syncthreads();
+    const uint32_t nh = min(nhot, kMidVerts);
+    if (threadIdx.x < m) {
+#pragma unroll
+        for (uint32_t k = 0; k < 2; k++) {
+            const uint32_t c = cnt[at[k]];
+            slot[2 * threadIdx.x + k] = (uint8_t)(c >= kPlaced ? c & 0xffu : kMidVerts);
+        }
+    }
+    for (uint32_t q = threadIdx.x; q < nh * per_v; q += kDirThreads) lds[q] = 0;
     __syncthreads();
     const uint32_t R = (kDirThreads / 2) / C;
     const uint32_t pair = threadIdx.x >> 1, w = threadIdx.x & 1;
@@ -858,10 +904,8 @@ __global__ __launch_bounds__(kDirThreads) void k_mid_scatter(const uint64_t *__r
     uint32_t nchanged = 0;
     if (i0 < R) {
         const uint64_t seed = sk.seeds[c];
-        for (uint32_t i = begin + i0; i < end; i += R) {
-            uint32_t e[2];
-            bool del;
-            unpack(upd[i], sk.V, e[0], e[1], del);
+        for (uint32_t i = i0; i < m; i += R) {
+            unpack(upd[begin + i], sk.V, e[0], e[1], del);
             const uint64_t x = (uint64_t)e[0] * sk.V + e[1];
             const uint64_t h = mix64(x ^ seed);
             const uint32_t d = depth_of(h, sk.D);
@@ -869,12 +913,9 @@ __global__ __launch_bounds__(kDirThreads) void k_mid_scatter(const uint64_t *__r
             const uint32_t q = (d * C + c) * 2 + w;
 #pragma unroll
             for (uint32_t k = 0; k < 2; k++) {
-                uint32_t m = kMidVerts;
-#pragma unroll
-                for (uint32_t t = 0; t < kMidVerts; t++)
-                    if (e[k] == hot[t]) m = t;
-                if (m < kMidVerts && d < kMidRows) {
-                    lxor(&lds[m * per_v + q], val);
+                const uint32_t p = slot[2 * i + k];
+                if (p < kMidVerts && d < kMidRows) {
+                    lxor(&lds[p * per_v + q], val);
                 } else {
                     gxor(sk.b + e[k] * DC * 2 + q, val);
                     nchanged += 1 - w;
@@ -883,14 +924,11 @@ __global__ __launch_bounds__(kDirThreads) void k_mid_scatter(const uint64_t *__r
         }
     }
     __syncthreads();
-    for (uint32_t q = threadIdx.x; q < kMidVerts * per_v; q += kDirThreads) {
+    for (uint32_t q = threadIdx.x; q < nh * per_v; q += kDirThreads) {
         const uint64_t val = lds[q];
         if (val == 0) continue;
-        const uint32_t m = q / per_v;
-        uint32_t e = hot[0];
-#pragma unroll
-        for (uint32_t t = 1; t < kMidVerts; t++) e = m == t ? hot[t] : e;
-        gxor(sk.b + e * DC * 2 + (q - m * per_v), val);
+        const uint32_t p = q / per_v;
+        gxor(sk.b + hot[p] * DC * 2 + (q - p * per_v), val);
         nchanged += 1 - (q & 1);
     }
     add_touched(touched, nchanged, (uint32_t *)lds);
@@ -900,8 +938,12 @@ hipError_t launch_mid_scatter(hipStream_t s, const uint64_t *upd, uint32_t n, De
                               const uint32_t *derr, unsigned long long *touched)
 {
     if (n == 0) return hipSuccess;
+    // updates per block: as many as leave 1,024 blocks (a vertex in every block
+    // serializes one atomic per block), at least 32 and enough for all lanes
+    uint32_t per = 32;
+    while (per < kMidMax && (per * sk.C < kDirThreads / 2 || (uint64_t)per * 1024 < n)) per *= 2;
     const size_t lds = (size_t)kMidVerts * kMidRows * sk.C * 16;
-    k_mid_scatter<<<(n + kMidPer - 1) / kMidPer, kDirThreads, lds, s>>>(upd, n, sk, derr, touched);
+    k_mid_scatter<<<(n + per - 1) / per, kDirThreads, lds, s>>>(upd, n, sk, derr, per, touched);
     return hipGetLastError();
 }
 

@@ -110,3 +110,19 @@ def test_autotuner_schedule_times_the_route_a_batch_takes(cupk):
     assert got[0][0] < 0.6 * got[1][0]
     for ms in got:
         assert ms[0] < 1.5 * ms[8] + 0.02
+
+
+@pytest.mark.parametrize("V,C,n", [(131072, 4, 70_000), (1 << 20, 4, 300_000), (65536, 0, 25_000)])
+def test_direct_scatter_gathers_shared_vertices(cupk, V, C, n):
+    """A tenth of the updates at one vertex costs little more than none."""
+    got = []
+    ctx = cupk.Context(V, C, seed=1)
+    _tree(ctx, V)
+    for hub in (0.0, 0.1):
+        p = _batch(V, n, hub)
+        _us(ctx, p, tries=1)
+        got.append(_us(ctx, p))
+    ctx.close()
+    print(f"V={V} C={C} n={n} uniform {got[0]:.1f} us, a tenth at one vertex {got[1]:.1f} us",
+          flush=True)
+    assert got[1] < 1.8 * got[0]

@@ -98,10 +98,11 @@ def test_levels_mode_on_every_route(cupk, route):
 @pytest.mark.parametrize("V,C,n", [
     # one block classifies up to 16,384 updates
     (65536, 16, 16384), (65536, 16, 16385),
-    # the direct scatter ends: n * (C + 21) against 250,000 + C * V / 2
-    (65536, 16, 20926), (65536, 16, 20927),
-    # n * C against 100,000
-    (3001, 20, 5000), (3001, 20, 5001)])
+    # the direct scatter ends: n * (C + 1) against 100,000 + V + C * V / 4
+    (65536, 16, 25158), (65536, 16, 25159), (3001, 20, 5619), (3001, 20, 5620),
+    # a block takes 32, 64, 128, 256 updates
+    (65536, 4, 32768), (65536, 4, 32769), (300_000, 3, 65537), (300_000, 3, 131073),
+    (70_001, 1, 20_000)])
 def test_batches_where_routes_meet(cupk, V, C, n, hub):
     S, D = 0x10AD + n, 12
     rng = np.random.default_rng(n)
