@@ -528,7 +528,7 @@ def er16384_leg(args, cupk, np, torch, streamgen):
     bpu = algorithmic_bytes_per_update(C)
     # the timed launches (every TIME_EVERY-th of the timed region)
     launches = max(1, ctr["timed_launches"])
-    kname = "k_tile_scatter" if args.mode == "staged" else "k_scatter_atomic"
+    kname = "k_tile_scatter_stag" if args.mode == "staged" else "k_scatter_atomic"
     avg_ms = ctr["scatter_ms"] / launches
     upd_per_launch = ctr["timed_updates"] / launches
     achieved = bpu * upd_per_launch / (avg_ms * 1e-3) / 1e9
@@ -868,7 +868,7 @@ def clusters_main(args, cupk, np, torch, streamgen):
                                                 geometry=geometry,
                                                 tune_sample=args.tune_sample)
     value = total / dt
-    kname = "k_tile_scatter" if args.mode == "staged" else "k_scatter_atomic"
+    kname = "k_tile_scatter_stag" if args.mode == "staged" else "k_scatter_atomic"
     launches = max(1, ctr["timed_launches"])
     avg_ms = ctr["scatter_ms"] / launches
     upd_per_launch = ctr["timed_updates"] / launches

@@ -1195,11 +1195,6 @@ int capture_graphs(cupk_ctx *ctx)
     return CUPK_OK;
 }
 
-// Device work of one pass over the updates [0, n) at d_upd: forest upload,
-// batch descriptor, classification (with the header copy) and scatter.  A
-// revert pass applies updates again to undo a speculative scatter (XOR
-// toggles back); it leaves the forest mirror alone and its flags are not
-// read.
 // The timer slot of the pass being enqueued (every time_kernels-th pass),
 // or null.
 static int take_timer(cupk_ctx *ctx, uint32_t n, cupk_ctx::TimerSlot **out)
@@ -1334,8 +1329,12 @@ static int enqueue_small_scatter(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t 
 }
 static const uint32_t *small_zero(cupk_ctx *ctx) { return &ctx->d_small->hdr[HDR_NFLAG]; }
 
-// hold: a small pass (ctx->small_pass afterwards) leaves its scatter to the
-// caller.
+// Device work of one pass over the updates [0, n) at d_upd: forest upload,
+// batch descriptor, classification (which writes its header to the host) and
+// scatter.  A revert pass applies updates again to undo a speculative scatter
+// (XOR toggles back); it leaves the forest mirror alone and its flags are not
+// read.  hold: a small pass (ctx->small_pass afterwards) leaves its scatter to
+// the caller.
 int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert, bool hold = false)
 {
     int rc = harvest_timers(ctx, false);
@@ -1351,10 +1350,10 @@ int enqueue_pass(cupk_ctx *ctx, const uint64_t *d_upd, uint32_t n, bool revert, 
     rc = ctx->small_pass ? delta_forest(ctx, &nd) : revert ? CUPK_OK : upload_forest(ctx);
     if (rc != CUPK_OK) return rc;
     if (ctx->small_pass) {
-        // two launches and one copy: classify into the result block, copy
-        // header + flags + positions to the host, scatter with device
-        // atomics (the previous small result was read before this pass:
-        // every pass waits for its header or for the whole stream)
+        // two launches: one block classifies and writes header, flags and
+        // positions to the host itself, then the direct scatter (the previous
+        // small result was read before this pass: every pass waits for its
+        // header or for the whole stream)
         uint32_t *derr = &ctx->d_small->hdr[HDR_ERR];
         HIPCHK(launch_small_classify(ctx->s, d_upd, n, ctx->V, ctx->d_lp, ctx->h_delta.p, nd,
                                      ctx->h_small, derr, ctx->d_hdr + HDR_SEQ,

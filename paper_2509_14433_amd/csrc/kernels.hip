@@ -1408,9 +1408,9 @@ hipError_t launch_fine(hipStream_t s, uint32_t grid_n, uint32_t V, const uint32_
 //
 // What bounds it.  Dense batches: VALU issue (busy all the time), 19
 // instructions per (record, column), 8 of them the two 64-bit products.  The
-// two LDS atomics beside them keep the LDS busy for 80% of the time; fewer bank
-// conflicts (rows padded to 16 words: 8 clocks per atomic instead of 10)
-// changed nothing.  Against one lane per (record, column) pair the record is
+// two LDS atomics beside them keep the LDS busy for 80 to 93% of the time;
+// fewer bank conflicts (rows padded to 16 words: 8 clocks per atomic instead of
+// 10) changed nothing.  Against one lane per (record, column) pair the record is
 // decoded once instead of read back from LDS (24 B) by each of its C lanes,
 // no lane idles (64 mod C did), the column seeds are C registers, the column
 // offset is the instruction's offset field, and the finalizer's last step
@@ -1730,10 +1730,10 @@ struct StagedRec {
 
 // XOR one (record, column) pair into the LDS delta (or HBM for a deep row).
 // colb = column * 8; RSB = bytes per LDS depth row; pg = gamma plane offset
-// in bytes; seed1 = mix64_head(column seed).  The depth is ctz of the hash's low word with a stop bit at
-// rfast = min(rows, D-1, 31); only when no bit below rfast is set (odds
-// 2^-rfast) is the full depth taken, and a depth >= rows goes to HBM with
-// device atomics.
+// in bytes; seed1 = mix64_head(column seed).  The depth is ctz of the hash's
+// low word with a stop bit at rfast = min(rows, D-1, 31); only when no bit
+// below rfast is set (odds 2^-rfast) is the full depth taken, and a depth >=
+// rows goes to HBM with device atomics.
 DEVI void tile_pair(uint8_t *lds8, uint32_t RSB, uint32_t pg, uint32_t rows, uint32_t rfast,
                     uint32_t stop, uint32_t colb, uint64_t seed1, const StagedRec &r,
                     const DevSketch &sk, uint32_t w0, uint64_t DC2, uint32_t &nchanged)
