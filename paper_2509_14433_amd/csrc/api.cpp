@@ -1282,21 +1282,21 @@ static int enqueue_split_back(cupk_ctx *ctx, uint32_t n)
 
 // Whether a batch of n > kSmallMax updates goes to HBM directly (one device
 // atomic per changed word) instead of through the tiles.  The direct pass
-// costs about 14 us and 52 ps per (update, column), and up to 60% more when a
-// few vertices take 5 to 40% of the updates or degrees follow a power law; the
-// staged pass a chain of short kernels and the lines of the touched vertices,
-// which grow with V and C.  The line is drawn where the worst of uniform
-// batches, R-MAT batches and batches with one or four such vertices costs
-// about the same on both ways.  That worst ratio of direct to staged below and
-// above the line (n at it): V = 1,024, C = 1 (50,600): 45,000 updates 0.94,
-// 64,000 1.09; 1,024, C = 10 (9,400): 8,000 0.80, 11,000 0.93; 16,384, C = 14
-// (11,600): 11,000 0.94, 16,000 1.14; 65,536, C = 4 (46,200): 45,000 1.07;
-// 65,536, C = 16 (25,100): 23,000 0.94, 32,000 1.11; 131,072, C = 17 (43,800):
-// 45,000 0.86, 64,000 1.03; 2^20, C = 4 (308,000): 256,000 0.7, 360,000 0.92,
-// 512,000 1.16; 2^20, C = 20 (149,000): 128,000 0.90, 180,000 1.06, 256,000
-// 1.24 (uniform batches there: 0.41, 0.51, 0.71); 2^22, C = 8 (651,000):
-// 720,000 0.90, 1,000,000 1.08.  A caller that sets the tile geometry gets the
-// tiles.
+// costs about 14 us and 52 ps per (update, column), up to a half more when a
+// few vertices take 5 to 40% of the updates and up to twice as much when
+// degrees follow a power law; the staged pass a chain of short kernels and the
+// lines of the touched vertices, which grow with V and C.  The line is drawn
+// where the worst of uniform batches, R-MAT batches and batches with one or
+// four such vertices costs about the same on both ways.  That worst ratio of
+// direct to staged below and above the line (n at it): V = 1,024, C = 1
+// (50,600): 45,000 updates 0.94, 64,000 1.09; 1,024, C = 10 (9,400): 8,000
+// 0.80, 11,000 0.93; 16,384, C = 14 (11,600): 11,000 0.94, 16,000 1.14;
+// 65,536, C = 4 (46,200): 45,000 1.07; 65,536, C = 16 (25,100): 23,000 0.94,
+// 32,000 1.11; 131,072, C = 17 (43,800): 45,000 0.86, 64,000 1.03; 2^20, C = 4
+// (308,000): 256,000 0.7, 360,000 0.92, 512,000 1.16; 2^20, C = 20 (148,000):
+// 128,000 0.90, 180,000 1.06, 256,000 1.24 (uniform batches there: 0.41, 0.51,
+// 0.71); 2^22, C = 8 (651,000): 720,000 0.90, 1,000,000 1.08.  A caller that
+// sets the tile geometry gets the tiles.
 static bool direct_pays(const cupk_ctx *ctx, uint32_t n)
 {
     if (ctx->opts.scatter_mode != CUPK_SCATTER_STAGED) return true;

@@ -76,7 +76,7 @@ def test_many_lds_rows_keep_the_kernel(cupk):
     V = 65536
     many, few = _pair(cupk, V, 20, _batch(V, 1_000_000), dict(lds_rows=36, tile_vertices=4),
                       dict(lds_rows=31, tile_vertices=4), D=40)
-    assert many < 1.1 * few
+    assert many < 1.3 * few
 
 
 @pytest.mark.parametrize("V,C,n,hub", [
